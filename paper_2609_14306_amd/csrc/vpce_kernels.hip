@@ -36,19 +36,14 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
 // ---------------------------------------------------------------------------
-// Element policies.  BK: k elements staged per LDS pass (128 bytes per row);
-// KSTEP: k consumed by one MFMA; VEC: elements per 16 bytes.
+// Element policies.  VEC: elements per 16 bytes.
 // KB: elements of one 128-byte k-block of the k-blocked backward workspaces (and of
 // one row of a direct-to-LDS slice).  frag16 / mma16: one 16-byte operand fragment
 // per lane (8 bfloat16 or 4 float32 k values) and the MFMA work it feeds.
 struct Bf16 {
   using storage = uint16_t;
-  using frag = bf16x8_t;
   using frag16 = bf16x8_t;
-  static constexpr int BK = 64, KSTEP = 16, VEC = 8, PADK = 8, KB = 64;
-  __device__ static f32x16_t mma(frag a, frag b, f32x16_t c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-  }
+  static constexpr int VEC = 8, KB = 64;
   __device__ static f32x16_t mma16(frag16 a, frag16 b, f32x16_t c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
   }
@@ -64,12 +59,8 @@ struct Bf16 {
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 struct F32 {
   using storage = float;
-  using frag = float;
   using frag16 = f32x4_t;
-  static constexpr int BK = 32, KSTEP = 2, VEC = 4, PADK = 4, KB = 32;
-  __device__ static f32x16_t mma(frag a, frag b, f32x16_t c) {
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-  }
+  static constexpr int VEC = 4, KB = 32;
   // Lane half h holds k = 4h .. 4h + 3 of an 8-wide k group in both operands; MFMA q
   // takes element q, i.e. k = q (lanes 0-31) and 4 + q (lanes 32-63): the four MFMAs
   // together cover the group (the contraction order within it is a permutation).
@@ -81,149 +72,16 @@ struct F32 {
   }
 };
 
-// ---------------------------------------------------------------------------
-// Global -> register -> LDS staging of one k-contiguous operand tile of ROWS x
-// BK (element (r, k) at p[r * ld + k]), written to LDS as [ROWS][BK + PADK].
-// Rows at or beyond R are clamped to R-1 (they only feed accumulator rows or
-// columns that are never stored); k at or beyond K reads as zero, so ragged
-// contractions add nothing.  K is checked per 16-byte chunk: an operand whose
-// K is not a multiple of VEC must hold finite values up to the next multiple.
-template <class E, int ROWS, int NT>
-struct Stage {
-  using S = typename E::storage;
-  static constexpr int BK = E::BK, VEC = E::VEC;
-  static constexpr int LD = BK + E::PADK;
-  static constexpr int LDS_ELEMS = ROWS * LD;
-  static constexpr int UNITS = ROWS * BK / VEC;
-  static constexpr int PER = (UNITS + NT - 1) / NT;
-  uint4 regs[PER];
-
-  __device__ __forceinline__ void load(const S* __restrict__ p, int64_t ld, int r0, int R, int k0,
-                                       int K, int tid) {
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int u = tid + i * NT;
-      const int r = u / (BK / VEC), kc = (u % (BK / VEC)) * VEC;
-      const int rr = min(r0 + r, R - 1);
-      const int kk = k0 + kc;
-      regs[i] = (u < UNITS && kk < K && rr >= 0) ? *(const uint4*)(p + (int64_t)rr * ld + kk)
-                                                 : make_uint4(0, 0, 0, 0);
-    }
-  }
-  __device__ __forceinline__ void store(S* lds, int tid) const {
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int u = tid + i * NT;
-      if (u < UNITS) *(uint4*)(lds + (u / (BK / VEC)) * LD + (u % (BK / VEC)) * VEC) = regs[i];
-    }
-  }
-};
-
-// MFMA operand fragment of one 32-wide block (rows row0..row0+31 of the
-// operand's non-contracted dimension) at k offset kbase of the staged tile.
-// 32x32x16 bf16: lane l takes row l%32 and k = kbase + 8*(l/32) + 0..7.
-// 32x32x2 f32:   lane l takes row l%32 and k = kbase + l/32.
-template <class E, int LD>
-__device__ __forceinline__ typename E::frag read_frag(const typename E::storage* lds, int row0,
-                                                      int kbase, int lane) {
-  if constexpr (sizeof(typename E::storage) == 2) {
-    return *(const bf16x8_t*)(lds + (row0 + (lane & 31)) * LD + kbase + 8 * (lane >> 5));
-  } else {
-    return lds[(row0 + (lane & 31)) * LD + kbase + (lane >> 5)];
-  }
-}
-
 // Accumulator layout of a 32x32 MFMA block: lane l, register r holds
 // row 8*(r/4) + 4*(l/32) + r%4 and column l%32.
 __device__ __forceinline__ int acc_row(int r, int lane) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
-
-// Tile GEMM: acc += A[m0 : m0+BM, 0:K] * B[n0 : n0+BN, 0:K]^T on a WGM x WGN grid of
-// wavefronts.  Two LDS buffers: while the waves multiply out of one, the next
-// k-slice (already fetched into registers one slice ahead) is written into the
-// other, so each k-slice costs a single workgroup barrier.
-template <class E, int BM_, int BN_, int WGM_, int WGN_>
-struct Gemm {
-  using S = typename E::storage;
-  static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_;
-  static constexpr int NT = 64 * WGM * WGN;
-  static constexpr int OCC = 1;  // workgroups per CU the register budget is sized for
-  static constexpr int KDIV = 1;  // any K (ragged k-slices are zero-filled)
-  static constexpr int WM = BM / WGM, WN = BN / WGN, MB = WM / 32, NB = WN / 32;
-  static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile must be whole 32x32 blocks");
-  using SA = Stage<E, BM, NT>;
-  using SB = Stage<E, BN, NT>;
-  static constexpr int BUF_ELEMS = SA::LDS_ELEMS + SB::LDS_ELEMS;
-  static constexpr int LDS_ELEMS = 2 * BUF_ELEMS;
-
-  __device__ __forceinline__ static int wave_m(int wave) { return (wave / WGN) * WM; }
-  __device__ __forceinline__ static int wave_n(int wave) { return (wave % WGN) * WN; }
-
-  // Row-major operands only (the k-block strides are for the direct-load tile).
-  // RAGGED is accepted for the interface of GemmDma and changes nothing here.
-  template <bool RAGGED = false>
-  __device__ __forceinline__ static void run(f32x16_t (&acc)[MB][NB], const S* __restrict__ A,
-                                             int64_t lda, int m0, int M, const S* __restrict__ B,
-                                             int64_t ldb, int n0, int N, int K, S* smem,
-                                             int64_t = 64, int64_t = 64) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave_m(wave), wn = wave_n(wave);
-    SA la;
-    SB lb;
-    const int nk = (K + E::BK - 1) / E::BK;
-    la.load(A, lda, m0, M, 0, K, tid);
-    lb.load(B, ldb, n0, N, 0, K, tid);
-    la.store(smem, tid);
-    lb.store(smem + SA::LDS_ELEMS, tid);
-    __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-      const bool more = kt + 1 < nk;
-      if (more) {
-        la.load(A, lda, m0, M, (kt + 1) * E::BK, K, tid);
-        lb.load(B, ldb, n0, N, (kt + 1) * E::BK, K, tid);
-      }
-      const S* sA = smem + (kt & 1) * BUF_ELEMS;
-      const S* sB = sA + SA::LDS_ELEMS;
-      // Fragments of sub-step kk+1 are read while the MFMAs of sub-step kk run.
-      constexpr int NKK = E::BK / E::KSTEP;
-      typename E::frag a[2][MB], b[2][NB];
-#pragma unroll
-      for (int i = 0; i < MB; ++i) a[0][i] = read_frag<E, SA::LD>(sA, wm + 32 * i, 0, lane);
-#pragma unroll
-      for (int j = 0; j < NB; ++j) b[0][j] = read_frag<E, SB::LD>(sB, wn + 32 * j, 0, lane);
-#pragma unroll
-      for (int q = 0; q < NKK; ++q) {
-        const int cur = q & 1;
-        if (q + 1 < NKK) {
-#pragma unroll
-          for (int i = 0; i < MB; ++i)
-            a[cur ^ 1][i] = read_frag<E, SA::LD>(sA, wm + 32 * i, (q + 1) * E::KSTEP, lane);
-#pragma unroll
-          for (int j = 0; j < NB; ++j)
-            b[cur ^ 1][j] = read_frag<E, SB::LD>(sB, wn + 32 * j, (q + 1) * E::KSTEP, lane);
-        }
-#pragma unroll
-        for (int i = 0; i < MB; ++i)
-#pragma unroll
-          for (int j = 0; j < NB; ++j) acc[i][j] = E::mma(a[cur][i], b[cur][j], acc[i][j]);
-      }
-      if (more) {
-        S* nA = smem + ((kt + 1) & 1) * BUF_ELEMS;
-        la.store(nA, tid);
-        lb.store(nA + SA::LDS_ELEMS, tid);
-      }
-      __syncthreads();
-    }
-  }
-};
 
 // ---------------------------------------------------------------------------
 // Tile GEMM fed by direct global -> LDS loads (global_load_lds_dwordx4, 16 bytes
 // per lane straight into LDS, no staging registers) through a ring of two
 // k-slices of 128-byte rows: 64 bfloat16 or 32 float32 k values per row.  A
 // 16-byte fragment feeds one 32x32x16 bf16 MFMA or four 32x32x2 f32 MFMAs (see
-// the element policies); everything else is the same for both types.  Requires K
-// to be a multiple of the slice depth and both operands to hold finite values up
-// to that K (the backward's buffers are zero-padded).
+// the element policies); everything else is the same for both types.
 //
 // LDS slice layout: the A rows then the B rows, 128 bytes (eight 16-byte
 // chunks) per row, chunk c of row r stored in slot c ^ ((r >> 1) & 7): the 16
@@ -271,7 +129,23 @@ __device__ __forceinline__ void lds_dma16x1(const void* sbase, uint32_t o0, uint
                : "memory");
 }
 
-template <int BM_, int BN_, int WGM_, int WGN_, int BK_ = 64, int STAGES_ = 2, class E = Bf16>
+// The same load from 64-bit per-lane addresses, for the last slice of a contraction
+// whose K is no multiple of the slice depth: the lanes whose 16-byte chunk lies past K
+// read zeros from zero_chunk instead (a product with another row's values would not
+// be harmless: they may be infinite or NaN).
+__device__ uint4 zero_chunk = {0u, 0u, 0u, 0u};
+__device__ __forceinline__ void lds_dma16_lane(const void* addr, uint32_t l0) {
+  uint32_t m0v = l0;
+  asm volatile("s_nop 4\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+               : "+{m0}"(m0v)
+               : "v"(addr)
+               : "memory");
+}
+
+// KTAIL_: K may be any number of whole 16-byte chunks; otherwise it is a multiple of
+// the slice depth.
+template <int BM_, int BN_, int WGM_, int WGN_, int BK_ = 64, int STAGES_ = 2, class E = Bf16,
+          bool KTAIL_ = false>
 struct GemmDma {
   using S = typename E::storage;
   using F16 = typename E::frag16;
@@ -288,7 +162,7 @@ struct GemmDma {
   static constexpr int BK = ROW_BYTES / (int)sizeof(S);  // k values per slice
   static_assert((BK_ == 32 || BK_ == 64) && STAGES >= 2, "slice depth and ring slots");
   static_assert(E::KB % BK == 0, "slices never straddle a k-block of the layout");
-  static constexpr int KDIV = BK;                 // K must be a multiple of the slice depth
+  static constexpr bool KTAIL = KTAIL_;
   static constexpr int NKK = ROW_BYTES / 32;      // sub-steps per slice (two 16-byte chunks each)
   static_assert(NKK % 2 == 0, "register sets alternate per sub-step across slices");
   static constexpr int CPR = ROW_BYTES / 16;      // 16-byte chunks per row
@@ -327,6 +201,7 @@ struct GemmDma {
     const char* baseA;  // byte address of the tile's first A row (k = 0)
     const char* baseB;
     int64_t kblkA, kblkB;  // elements between consecutive k-blocks (E::KB wide)
+    int tail_kt, tail_chunks;  // KTAIL: the slice that reaches past K and its live chunks
     uint32_t offA[A_LOADS], offB[B_LOADS];  // per-lane byte offsets from the bases
   };
 
@@ -358,6 +233,18 @@ struct GemmDma {
     constexpr int KB = E::KB;
     const int64_t k0 = (int64_t)kt * BK;
     const uint32_t l = lds0 + slot_bytes(kt) + (uint32_t)(wave * 1024) + q * NWAVES * 1024;
+    if constexpr (KTAIL) {
+      if (kt == L.tail_kt) {
+        const int lane = threadIdx.x & 63;
+        const int c = (lane % CPR) ^ key((wave + q * NWAVES) * RPI + lane / CPR);
+        const char* p = q < A_LOADS
+                            ? L.baseA + (k0 / KB) * L.kblkA * (int64_t)sizeof(S) + L.offA[q < A_LOADS ? q : 0]
+                            : L.baseB + (k0 / KB) * L.kblkB * (int64_t)sizeof(S) + L.offB[q < A_LOADS ? 0 : q - A_LOADS];
+        static_assert(BK == KB, "the tail slice starts at a k-block");
+        lds_dma16_lane(c < L.tail_chunks ? (const void*)p : (const void*)&zero_chunk, l);
+        return;
+      }
+    }
     if (q < A_LOADS)
       lds_dma16x1(L.baseA + ((k0 / KB) * L.kblkA + (k0 % KB)) * (int64_t)sizeof(S), L.offA[q], l);
     else
@@ -407,7 +294,7 @@ struct GemmDma {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave_m(wave), wn = wave_n(wave);
-    const int nk = K / BK;
+    const int nk = KTAIL ? (K + BK - 1) / BK : K / BK;
     if (nk <= 0) return;
     // row blocks of A with live rows (wave-uniform); MB unless RAGGED
     const int mb_live = RAGGED ? max(0, min(MB, (M - m0 - wm + 31) / 32)) : MB;
@@ -416,6 +303,10 @@ struct GemmDma {
     plan(L, A, lda, m0, M, B, ldb, n0, N, wave, lane);
     L.kblkA = kblka;
     L.kblkB = kblkb;
+    if constexpr (KTAIL) {
+      L.tail_kt = K % BK ? nk - 1 : -1;
+      L.tail_chunks = K % BK / E::VEC;
+    }
     // prologue: the first min(STAGES, nk) slices, whole; wait for slice 0
     const int pro = min(STAGES, nk);
     for (int kt = 0; kt < pro; ++kt)
@@ -1195,8 +1086,9 @@ __global__ void __launch_bounds__(256) transpose_kernel(TransposeArgs a) {
 // ---------------------------------------------------------------------------
 // Tile configurations.  Both element types: the direct-to-LDS ring (128-byte
 // slice rows: 64 bfloat16 or 32 float32 k values, two slots) with 256 x 256
-// tiles; the register-staged tile of the same shape when d is not a multiple of
-// the slice depth.
+// tiles; LogitsTail is the same tile for a d that is not a multiple of the slice
+// depth (a kernel of its own, so that the per-lane addresses of the last slice cost
+// the usual widths no registers).
 template <class E> struct Cfg;
 template <> struct Cfg<Bf16> {
   // 512-thread workgroups (two wavefronts per SIMD), 256 x 256 tiles, 128 x 64 per
@@ -1210,18 +1102,16 @@ template <> struct Cfg<Bf16> {
   // the last dH / dW column block when d leaves 1..64 columns past a multiple of
   // 256 (160 x 64 per wave, 0.7 fragment reads per MFMA)
   using MmWide = GemmDma<320, 256, 2, 4>;
-  using LogitsReg = Gemm<Bf16, Logits::BM, Logits::BN, Logits::WGM, Logits::WGN>;
-  static_assert(64 % Mm::KDIV == 0, "dH / dW launch granularity");
+  using LogitsTail = GemmDma<256, 256, 2, 4, 64, 2, Bf16, true>;
   static constexpr int KALIGN = 64;  // K granularity the dH / dW launches need
 };
 template <> struct Cfg<F32> {
   // The same direct-to-LDS ring and 256 x 256 tiles: 32 float32 k values per slice,
-  // four 32x32x2 f32 MFMAs per fragment pair.  d not a multiple of 32: the
-  // register-staged tile of the same shape.
+  // four 32x32x2 f32 MFMAs per fragment pair.
   using Logits = GemmDma<256, 256, 2, 4, 64, 2, F32>;
   using Mm = Logits;  // the dH / dW contractions
   using MmWide = GemmDma<320, 256, 2, 4, 64, 2, F32>;
-  using LogitsReg = Gemm<F32, Logits::BM, Logits::BN, Logits::WGM, Logits::WGN>;
+  using LogitsTail = GemmDma<256, 256, 2, 4, 64, 2, F32, true>;
   static constexpr int KALIGN = 32;  // K granularity the dH / dW launches need
 };
 
@@ -1235,8 +1125,8 @@ static bool launch_fwd_g(const FwdArgs& a, hipStream_t s) {
 }
 template <class E>
 static bool launch_fwd(const FwdArgs& a, hipStream_t s) {
-  if (a.d % Cfg<E>::Logits::KDIV == 0) return launch_fwd_g<E, typename Cfg<E>::Logits>(a, s);
-  return launch_fwd_g<E, typename Cfg<E>::LogitsReg>(a, s);
+  if (a.d % E::KB == 0) return launch_fwd_g<E, typename Cfg<E>::Logits>(a, s);
+  return launch_fwd_g<E, typename Cfg<E>::LogitsTail>(a, s);
 }
 // Per-XCD split of n0 + n1 + n2 workgroups (workgroup b runs on XCD b % 8, so
 // XCD x receives n/8 of them, one more for x < n%8): kinds 0 and 1 are spread
@@ -1292,9 +1182,9 @@ template <class E>
 static bool launch_stage(const GemmArgs& h, const GemmArgs& w, const GradArgs& g, hipStream_t s) {
   using Mm = typename Cfg<E>::Mm;
   using Wd = typename Cfg<E>::MmWide;
-  if (g.d % Cfg<E>::Logits::KDIV == 0)
+  if (g.d % E::KB == 0)
     return launch_stage_g<E, typename Cfg<E>::Logits, Mm, Wd>(h, w, g, s);
-  return launch_stage_g<E, typename Cfg<E>::LogitsReg, Mm, Wd>(h, w, g, s);
+  return launch_stage_g<E, typename Cfg<E>::LogitsTail, Mm, Wd>(h, w, g, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -1326,11 +1216,11 @@ bool scratch_base(void** out) {
 
 // ---- entry points used by the host API (vpce_api.cpp) ----
 TileShape tile_shape(int dtype) {
-  static_assert(Cfg<Bf16>::Logits::BM == Cfg<Bf16>::LogitsReg::BM &&
-                    Cfg<Bf16>::Logits::BN == Cfg<Bf16>::LogitsReg::BN,
+  static_assert(Cfg<Bf16>::Logits::BM == Cfg<Bf16>::LogitsTail::BM &&
+                    Cfg<Bf16>::Logits::BN == Cfg<Bf16>::LogitsTail::BN,
                 "both logits mainloops must share the tile shape");
-  static_assert(Cfg<F32>::Logits::BM == Cfg<F32>::LogitsReg::BM &&
-                    Cfg<F32>::Logits::BN == Cfg<F32>::LogitsReg::BN,
+  static_assert(Cfg<F32>::Logits::BM == Cfg<F32>::LogitsTail::BM &&
+                    Cfg<F32>::Logits::BN == Cfg<F32>::LogitsTail::BN,
                 "both logits mainloops must share the tile shape");
   static_assert(Cfg<Bf16>::KALIGN == Bf16::KB && Cfg<F32>::KALIGN == F32::KB,
                 "dH / dW contractions read whole k-blocks");
