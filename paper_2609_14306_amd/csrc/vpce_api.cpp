@@ -61,10 +61,10 @@ vp_status validate(const vp_problem* p, int64_t* V_out, bool allow_empty_vocab =
 
 inline bool misaligned(const void* ptr) { return ((uintptr_t)ptr & 15u) != 0; }
 
-// Vocabulary splits of the forward: workgroup (token block, split) folds one token
-// block over one contiguous range of the vocabulary tiles, and an XCD runs 32
-// consecutive workgroups at a time, i.e. 32 / S token blocks by S splits.  S is the
-// smallest power of two (at most 32) that
+// Vocabulary splits of the forward on 256 x 256 tiles: workgroup (token block, split)
+// folds one token block over one contiguous range of the vocabulary tiles, and an XCD
+// runs 32 consecutive workgroups at a time, i.e. 32 / S token blocks by S splits.  S
+// is the smallest power of two (at most 32) that
 // - fills the CUs (token blocks x S >= 256);
 // - is at least 4, so that those 32 tiles share 12 operand panels in the XCD's L2
 //   (8 x 4 or 4 x 8);
@@ -82,10 +82,69 @@ int splits_for(const vp_problem* p) {
   return s;
 }
 
-size_t fwd_ws_bytes(const vp_problem* p) {
-  const size_t T = (size_t)p->T;
-  const size_t S = (size_t)splits_for(p);
-  return kHeaderBytes + 2 * align256(S * T * 4) + align256(T * 4);
+// Few tokens: at most kFewTokens = 256 CUs / 32 splits x 256 tokens, where 32 splits
+// no longer give every CU a workgroup.  There the forward may take more splits and
+// smaller tiles (plan_fwd); the partial states it may write per call (splits x T) are
+// at least what 32 splits need, and otherwise the 64 Ki that 32 splits take at
+// kFewTokens, but no more than a quarter of the bytes of H itself (8 bytes each) or
+// 8 Ki, whichever is larger.  The count never falls as T grows.
+constexpr int64_t kFewTokens = 2048;
+int64_t partial_slots(const vp_problem* p) {
+  const int64_t T = p->T, base = (int64_t)splits_for(p) * T;
+  if (T == 0 || T > kFewTokens) return base;
+  const int64_t quarter = T * p->d * (int64_t)elem_bytes(p->dtype) / 32;
+  return std::max(base, std::min<int64_t>(32 * kFewTokens, std::max<int64_t>(8192, quarter)));
+}
+size_t fwd_bytes(int64_t slots, int64_t T) {
+  return kHeaderBytes + 2 * align256((size_t)slots * 4) + align256((size_t)T * 4);
+}
+
+size_t fwd_ws_bytes(const vp_problem* p) { return fwd_bytes(partial_slots(p), p->T); }
+// What the forward needs at least: the partial states of splits_for() splits.
+size_t fwd_ws_min(const vp_problem* p) {
+  return fwd_bytes((int64_t)splits_for(p) * p->T, p->T);
+}
+
+// Vocabulary tiles of `bm` rows over all shards.
+int64_t count_tiles(const vp_problem* p, int bm) {
+  int64_t n = 0;
+  for (int q = 0; q < p->P; ++q) n += ceil_div(p->shard_rows[q], bm);
+  return n;
+}
+
+// Tile kind and splits of a forward over the problem's shards with room for `slots`
+// partial states.  Above kFewTokens tokens the 256 x 256 tile with splits_for() splits.
+// Below, the kind whose launch is estimated shortest: every workgroup runs
+// ceil(tiles / splits) tiles one after the other, the launch takes ceil(workgroups /
+// places on the chip) such turns, and a tile takes d / slice depth times the measured
+// time per slice of its kind (the same d for every kind, so it is left out).  Measured
+// both ways (microseconds, kinds 0 / 1 / 2): d = 4096, V = 151936 in 16 shards, bf16:
+// T = 40: 310 / 258 / 245, T = 100: 308 / 267 / 348, T = 256: 333 / 425 / 608, T = 1024:
+// 1071 / 1470 / 2261; d = 1000, V = 32003 in 5: T = 40: 36 / 31 / 27, T = 300: 87 / 70 /
+// 54; float32 d = 2880, V = 50000 in 4: T = 64: 668 / 399 / 248, T = 1024: 2612 / 2686 /
+// 2900.  With at most 32 splits of 256 x 256 tiles the first of these took 1550.
+struct FwdPlan {
+  int kind, splits;
+};
+FwdPlan plan_fwd(const vp_problem* p, int64_t slots) {
+  FwdPlan best{0, splits_for(p)};
+  if (p->T > kFewTokens) return best;
+  double best_time = 0;
+  for (int kind = 0; kind < vpce::kFwdKinds; ++kind) {
+    const vpce::FwdTile t = vpce::fwd_tile(p->dtype, kind);
+    const int64_t blocks = ceil_div(p->T, t.bn), places = kCUs * t.per_cu;
+    const int64_t tiles = std::max<int64_t>(1, count_tiles(p, t.bm));
+    int64_t S = std::max<int64_t>(1, std::min(std::min(slots / p->T, places / blocks), tiles));
+    const int64_t turn = ceil_div(tiles, S);
+    S = ceil_div(tiles, turn);  // the same turns with the fewest splits
+    const double time = (double)(turn * ceil_div(blocks * S, places)) *
+                        std::max(t.shared, blocks == 1 ? t.stream : 0.0);
+    if (kind == 0 || time < best_time) {
+      best = FwdPlan{kind, (int)S};
+      best_time = time;
+    }
+  }
+  return best;
 }
 
 // Backward plan.  The softmax residual of a strip of Tc tokens by Vc
@@ -242,27 +301,35 @@ vp_status check_forward(const vp_problem* prob, const void* H, const void* const
   return VP_OK;
 }
 
-// The forward on a checked problem, with a workspace of at least fwd_ws_bytes(prob).
+// Partial states a workspace of ws_bytes >= fwd_ws_min(p) is used for: a caller that
+// sized it with vp_ce_workspace_size gets all of partial_slots, whatever it has beyond.
+int64_t slots_in(const vp_problem* p, size_t ws_bytes) {
+  return ws_bytes >= fwd_ws_bytes(p) ? partial_slots(p) : (int64_t)splits_for(p) * p->T;
+}
+
+// The forward on a checked problem, with a workspace of at least fwd_ws_min(prob) bytes.
 vp_status forward_impl(const vp_problem* prob, int64_t V, const void* H,
                        const void* const* W_shards, const int64_t* targets, float* loss,
-                       float* lse, void* ws, hipStream_t s) {
+                       float* lse, void* ws, size_t ws_bytes, hipStream_t s) {
   const int64_t T = prob->T;
   unsigned long long* counter = (unsigned long long*)ws;
-  if (!vpce::run_ws_init(counter, s)) return VP_ERR_HIP;
-  if (T == 0) return VP_OK;
+  if (T == 0) return vpce::run_ws_init(counter, s) ? VP_OK : VP_ERR_HIP;
 
-  const vpce::TileShape ts = vpce::tile_shape(prob->dtype);
-  const int S = splits_for(prob);
+  const FwdPlan plan = plan_fwd(prob, slots_in(prob, ws_bytes));
+  const vpce::FwdTile ft = vpce::fwd_tile(prob->dtype, plan.kind);
+  const int S = plan.splits;
   char* base = (char*)ws + kHeaderBytes;
   vpce::FwdArgs a;
   memset(&a, 0, sizeof(a));
-  build_table(prob, W_shards, ts.fwd_bm, &a.st, &a.n_tiles);
+  build_table(prob, W_shards, ft.bm, &a.st, &a.n_tiles);
   a.H = H;
   a.targets = targets;
   a.T = T;
   a.d = (int32_t)prob->d;
-  a.n_tok_blocks = (int32_t)ceil_div(T, ts.fwd_bn);
+  a.n_tok_blocks = (int32_t)ceil_div(T, ft.bn);
   a.n_splits = S;
+  a.kind = plan.kind;
+  a.counter = counter;
   a.m_part = (float*)base;
   a.s_part = (float*)(base + align256((size_t)S * T * 4));
   a.y_tgt = (float*)(base + 2 * align256((size_t)S * T * 4));
@@ -296,10 +363,11 @@ vp_status vp_ce_forward(const vp_problem* prob, const void* H, const void* const
   if (st != VP_OK) return st;
   if ((st = check_shards(prob, W_shards)) != VP_OK) return st;
   if (!ws) return VP_ERR_WORKSPACE;
-  if (ws_bytes < fwd_ws_bytes(prob)) return VP_ERR_WORKSPACE;
+  if (ws_bytes < fwd_ws_min(prob)) return VP_ERR_WORKSPACE;
   if (misaligned(ws)) return VP_ERR_ALIGN;
   if ((st = check_forward(prob, H, W_shards, targets, loss, lse, &V)) != VP_OK) return st;
-  return forward_impl(prob, V, H, W_shards, targets, loss, lse, ws, (hipStream_t)stream);
+  return forward_impl(prob, V, H, W_shards, targets, loss, lse, ws, ws_bytes,
+                      (hipStream_t)stream);
 }
 
 vp_status vp_ce_forward_noalloc(const vp_problem* prob, const void* H,
@@ -308,10 +376,11 @@ vp_status vp_ce_forward_noalloc(const vp_problem* prob, const void* H,
   int64_t V = 0;
   const vp_status st = check_forward(prob, H, W_shards, targets, loss, lse, &V);
   if (st != VP_OK) return st;
-  if (fwd_ws_bytes(prob) > vpce::kScratchBytes) return VP_ERR_WORKSPACE;
+  if (fwd_ws_min(prob) > vpce::kScratchBytes) return VP_ERR_WORKSPACE;
   void* ws = nullptr;
   if (!vpce::scratch_base(&ws)) return VP_ERR_HIP;
-  return forward_impl(prob, V, H, W_shards, targets, loss, lse, ws, (hipStream_t)stream);
+  return forward_impl(prob, V, H, W_shards, targets, loss, lse, ws, vpce::kScratchBytes,
+                      (hipStream_t)stream);
 }
 
 vp_status vp_ce_state_init(float* state, int64_t T, void* stream) {
@@ -334,16 +403,17 @@ vp_status vp_ce_fold_shard(const vp_problem* shard, int64_t id_offset, const voi
   // an empty strip leaves the state unchanged: nothing is launched, nothing is read
   if (T == 0 || Vq == 0) return VP_OK;
   if (!ws) return VP_ERR_WORKSPACE;
-  if (ws_bytes < fwd_ws_bytes(shard)) return VP_ERR_WORKSPACE;
+  if (ws_bytes < fwd_ws_min(shard)) return VP_ERR_WORKSPACE;
   if (misaligned(ws)) return VP_ERR_ALIGN;
   if (!H || !W_shard || !targets || !state) return VP_ERR_NULL;
   if (misaligned(H) || misaligned(W_shard)) return VP_ERR_ALIGN;
   if (((uintptr_t)state & 3u) != 0) return VP_ERR_ALIGN;
   hipStream_t s = (hipStream_t)stream;
 
-  const vpce::TileShape ts = vpce::tile_shape(shard->dtype);
-  const int32_t tiles = (int32_t)ceil_div(Vq, ts.fwd_bm);
-  const int S = std::min(splits_for(shard), (int)tiles);
+  const FwdPlan plan = plan_fwd(shard, slots_in(shard, ws_bytes));
+  const vpce::FwdTile ft = vpce::fwd_tile(shard->dtype, plan.kind);
+  const int32_t tiles = (int32_t)ceil_div(Vq, ft.bm);
+  const int S = std::min(plan.splits, (int)tiles);
   char* base = (char*)ws + kHeaderBytes;
   vpce::FwdArgs a;
   memset(&a, 0, sizeof(a));
@@ -359,8 +429,9 @@ vp_status vp_ce_fold_shard(const vp_problem* shard, int64_t id_offset, const voi
   a.targets = targets;
   a.T = T;
   a.d = (int32_t)shard->d;
-  a.n_tok_blocks = (int32_t)ceil_div(T, ts.fwd_bn);
+  a.n_tok_blocks = (int32_t)ceil_div(T, ft.bn);
   a.n_splits = S;
+  a.kind = plan.kind;
   a.m_part = (float*)base;
   a.s_part = (float*)(base + align256((size_t)S * T * 4));
   a.y_tgt = state + 2 * T;  // written only for targets this shard owns

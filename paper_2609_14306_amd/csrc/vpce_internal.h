@@ -25,6 +25,8 @@ struct FwdArgs {
   int64_t T;
   int32_t d;
   int32_t n_tok_blocks, n_splits, n_tiles;
+  int32_t kind;                 // tile of the kernel (see fwd_tile)
+  unsigned long long* counter;  // cleared by the kernel for the merge that follows; may be null
   float* m_part;  // [n_splits][T]
   float* s_part;  // [n_splits][T]
   float* y_tgt;   // [T]
@@ -133,6 +135,16 @@ struct TileShape {
 };
 
 TileShape tile_shape(int dtype);
+
+// Tiles the forward can run on: kind 0 is the 256 x 256 tile of every large problem,
+// the others are the streamed tiles for few tokens.
+constexpr int kFwdKinds = 3;
+struct FwdTile {
+  int bm, bn;             // vocabulary rows by tokens
+  int per_cu;             // workgroups a CU holds
+  double shared, stream;  // time per slice: W shared by several token blocks, or by none
+};
+FwdTile fwd_tile(int dtype, int kind);
 
 // Bytes of the library-owned device workspace of vp_ce_forward_noalloc.
 constexpr size_t kScratchBytes = 16u << 20;

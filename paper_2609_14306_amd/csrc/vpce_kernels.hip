@@ -385,6 +385,88 @@ struct GemmDma {
 };
 
 // ---------------------------------------------------------------------------
+// Small tiles for problems whose 256 x 256 tiles would leave most of the chip idle or
+// be mostly padding: the same slices, swizzle and direct-to-LDS loads, but a ring of
+// STAGES slices of which all but one are in flight, and one plain loop over slices
+// (wait, barrier, refill, multiply).  What bounds these problems is the stream of W
+// from memory: a CU keeps (STAGES - 1) slices of it in flight, and the ring runs on
+// across tile boundaries (stream_fwd), so that no tile starts on an empty pipe.
+template <int BM_, int BN_, int WGM_, int WGN_, int STAGES_, class E>
+struct Ring {
+  using S = typename E::storage;
+  using F16 = typename E::frag16;
+  static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_, STAGES = STAGES_;
+  static constexpr int NT = 64 * WGM * WGN, NWAVES = WGM * WGN;
+  static constexpr int WM = BM / WGM, WN = BN / WGN, MB = WM / 32, NB = WN / 32;
+  static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile must be whole 32x32 blocks");
+  static constexpr int BK = E::KB, CPR = 8;  // 128-byte slice rows of eight 16-byte chunks
+  static constexpr int SLICE_BYTES = (BM + BN) * 128;
+  static constexpr int LDS_BYTES = STAGES * SLICE_BYTES;
+  static constexpr int OCC = LDS_BYTES <= 80 * 1024 ? 2 : 1;  // workgroups per CU
+  static constexpr int A_LOADS = BM / 8 / NWAVES, B_LOADS = BN / 8 / NWAVES;
+  static_assert(BM % (8 * NWAVES) == 0 && BN % (8 * NWAVES) == 0, "whole load groups per wave");
+  static constexpr int NLOADS = A_LOADS + B_LOADS;
+  static_assert(STAGES >= 3 && (STAGES - 2) * NLOADS < 64 && LDS_BYTES <= 160 * 1024, "ring");
+  static_assert(2 * WGM * BN * 4 <= LDS_BYTES, "write_partials' exchange");
+
+  __device__ __forceinline__ static int wave_m(int wave) { return (wave / WGN) * WM; }
+  __device__ __forceinline__ static int wave_n(int wave) { return (wave % WGN) * WN; }
+  __device__ __forceinline__ static int key(int r) { return (r >> 1) & 7; }
+
+  // Per-lane byte offsets of an operand's loads: load q of a wave covers the eight rows
+  // from (wave + q * NWAVES) * 8; rows at or past `rows` repeat the last one.
+  template <int N>
+  __device__ __forceinline__ static void offsets(uint32_t (&off)[N], int rows, int64_t ld, int wave,
+                                                 int lane) {
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+      const int r = (wave + q * NWAVES) * 8 + lane / 8;
+      off[q] = (uint32_t)(min(r, rows - 1) * ld * (int64_t)sizeof(S)) + 16u * ((lane & 7) ^ key(r));
+    }
+  }
+  // The loads of one operand's part of a slice into LDS at l0.  chunks: live 16-byte
+  // chunks of the slice's rows (8, or fewer where the slice reaches past K: those read
+  // zeros).
+  template <int N>
+  __device__ __forceinline__ static void issue(const char* base, const uint32_t (&off)[N],
+                                               int chunks, uint32_t l0, int wave, int lane) {
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+      const uint32_t l = l0 + (uint32_t)(wave + q * NWAVES) * 1024u;
+      if (chunks == CPR) {
+        lds_dma16x1(base, off[q], l);
+      } else {
+        const int c = (lane & 7) ^ key((wave + q * NWAVES) * 8 + lane / 8);
+        lds_dma16_lane(c < chunks ? (const void*)(base + off[q]) : (const void*)&zero_chunk, l);
+      }
+    }
+  }
+  // acc += the product of one slice at LDS address `slot` (A rows, then B rows).
+  __device__ __forceinline__ static void multiply(f32x16_t (&acc)[MB][NB], const char* slot, int wm,
+                                                  int wn, int lane) {
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      const int chunk = 2 * kk + (lane >> 5);
+      F16 fa[MB], fb[NB];
+#pragma unroll
+      for (int i = 0; i < MB; ++i) {
+        const int r = wm + 32 * i + (lane & 31);
+        fa[i] = *(const F16*)(slot + r * 128 + ((chunk ^ key(r)) << 4));
+      }
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        const int r = wn + 32 * j + (lane & 31);
+        fb[j] = *(const F16*)(slot + (BM + r) * 128 + ((chunk ^ key(r)) << 4));
+      }
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[i][j] = E::mma16(fa[i], fb[j], acc[i][j]);
+    }
+  }
+};
+
+// ---------------------------------------------------------------------------
 // Workgroup -> tile mapping.  Workgroups are dispatched to the 8 XCDs round
 // robin (workgroup i on XCD i % 8) and each XCD has its own L2, so consecutive
 // logical tile ids are handed to the workgroups of one XCD: the tiles an XCD
@@ -411,13 +493,36 @@ __device__ __forceinline__ void grouped_tile(int logical, int n_m, int n_n, int 
 
 // ---------------------------------------------------------------------------
 // Online-softmax state merge in the base-2 domain (m is a running maximum of
-// y*log2(e), s = sum 2^(y*log2e - m)).  An empty state is (-inf, 0).
+// y*log2(e), s = sum 2^(y*log2e - m)).  An empty state is (-inf, 0); merging two of
+// them stays empty.
 __device__ __forceinline__ void merge_state(float& m, float& s, float mo, float so) {
   const float M = fmaxf(m, mo);
-  if (M == -INFINITY) return;
-  s = s * __builtin_amdgcn_exp2f(m - M) + so * __builtin_amdgcn_exp2f(mo - M);
+  const float ref = M == -INFINITY ? 0.f : M;
+  s = s * __builtin_amdgcn_exp2f(m - ref) + so * __builtin_amdgcn_exp2f(mo - ref);
   m = M;
 }
+
+// Folds the partial states of `n` splits of token t, LPT consecutive lanes per token:
+// lane l of them takes splits l, l + LPT, ... in visiting order, then the lanes merge.
+// Every lane of the group ends with the whole state.
+template <int LPT>
+__device__ __forceinline__ void merge_splits(const float* __restrict__ mp,
+                                             const float* __restrict__ sp, int64_t T, int64_t t,
+                                             int n, float& m, float& s) {
+  m = -INFINITY;
+  s = 0.f;
+#pragma unroll 4
+  for (int k = threadIdx.x % LPT; k < n; k += LPT)
+    merge_state(m, s, mp[(int64_t)k * T + t], sp[(int64_t)k * T + t]);
+#pragma unroll
+  for (int o = 1; o < LPT; o <<= 1) {
+    const float mo = __shfl_xor(m, o), so = __shfl_xor(s, o);
+    merge_state(m, s, mo, so);
+  }
+}
+// Lanes per token of the merges: with many splits (few tokens) one thread per token
+// would walk them serially on a nearly idle chip (32 splits at T = 256: 10.8 us).
+constexpr int kManySplits = 16;
 
 __global__ void ws_init_kernel(unsigned long long* counter) {
   if (threadIdx.x == 0 && blockIdx.x == 0) *counter = 0ull;
@@ -426,6 +531,115 @@ __global__ void ws_init_kernel(unsigned long long* counter) {
 __global__ void fill_zero_kernel(float* p, int64_t n) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = 0.f;
+}
+
+// Folds column block j of a logits tile into this lane's running state.  Tiles past
+// the end of a shard mask their padded rows; full tiles (all but the last of each
+// shard) take the select-free loops.  Register r of row block i holds tile row
+// wm + 32 i + acc_row(r, lane) = wm + 4 (lane / 32) + (a constant), so the mask
+// compares that constant with one per-lane limit.
+template <int MB, int NB>
+__device__ __forceinline__ void fold_column(const f32x16_t (&acc)[MB][NB], int j, bool full,
+                                            int lim, float& m_run, float& s_run) {
+  // The maximum is taken on the raw logits and scaled once: scaling by a positive
+  // constant is monotone under rounding, so this equals the maximum of the scaled
+  // values.
+  float tmax = -INFINITY;
+  if (full) {
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, acc[i][j][r]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (32 * i + 8 * (r >> 2) + (r & 3) < lim) tmax = fmaxf(tmax, acc[i][j][r]);
+  }
+  tmax *= kLog2e;
+  const float scale = tmax > m_run ? __builtin_amdgcn_exp2f(m_run - tmax) : 1.f;
+  m_run = fmaxf(m_run, tmax);
+  float sum = 0.f;
+  if (full) {
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        sum += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][j][r], kLog2e, -m_run));
+  } else {
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][j][r], kLog2e, -m_run));
+        sum += (32 * i + 8 * (r >> 2) + (r & 3) < lim) ? e : 0.f;
+      }
+  }
+  s_run = s_run * scale + sum;
+}
+
+// Target gather of column block j: exactly one tile in the whole vocabulary holds a
+// token's target; the lane that owns that element stores the logit.  relw: the
+// target's row in this wave's WM rows (outside them: not here).
+template <int MB, int NB>
+__device__ __forceinline__ void gather_target(const f32x16_t (&acc)[MB][NB], int j, int64_t rel,
+                                              int rows, int wm, int lane, float* y) {
+  if (rel >= 0 && rel < rows) {
+    const int relw = (int)rel - wm;
+    if (relw >= 0 && relw < 32 * MB) {
+      const int rib = relw & 31;
+      if (((rib >> 2) & 1) == (lane >> 5)) {
+        const int want_i = relw >> 5, want_r = (rib >> 3) * 4 + (rib & 3);
+        float yv = 0.f;
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) yv = (i == want_i && r == want_r) ? acc[i][j][r] : yv;
+        *y = yv;
+      }
+    }
+  }
+}
+
+// End of a forward workgroup: merges the two lane halves that share a token column,
+// then the wave rows, and writes the workgroup's partial state per token.  LDS must
+// be idle; the header's counter is cleared for the merge kernel that follows.
+template <class G>
+__device__ __forceinline__ void write_partials(const FwdArgs& a, float (&m_run)[G::NB],
+                                               float (&s_run)[G::NB], int split, int n0, float* red) {
+  constexpr int BN = G::BN, NB = G::NB;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wn = G::wave_n(wave);
+#pragma unroll
+  for (int j = 0; j < NB; ++j) {
+    const float mo = __shfl_xor(m_run[j], 32);
+    const float so = __shfl_xor(s_run[j], 32);
+    merge_state(m_run[j], s_run[j], mo, so);
+  }
+  __syncthreads();
+  const int wr = wave / G::WGN;  // red: [WGM][2][BN]
+  if (lane < 32) {
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      red[(wr * 2) * BN + wn + 32 * j + lane] = m_run[j];
+      red[(wr * 2 + 1) * BN + wn + 32 * j + lane] = s_run[j];
+    }
+  }
+  __syncthreads();
+  if (wr == 0 && lane < 32) {
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const int c = wn + 32 * j + lane;
+      for (int w2 = 1; w2 < G::WGM; ++w2)
+        merge_state(m_run[j], s_run[j], red[(w2 * 2) * BN + c], red[(w2 * 2 + 1) * BN + c]);
+      const int64_t n = n0 + c;
+      if (n < a.T) {
+        a.m_part[(int64_t)split * a.T + n] = m_run[j];
+        a.s_part[(int64_t)split * a.T + n] = s_run[j];
+      }
+    }
+  }
+  if (blockIdx.x == 0 && tid == 0 && a.counter) *a.counter = 0ull;
 }
 
 // Forward: each workgroup owns BN tokens and one contiguous range of the
@@ -473,112 +687,131 @@ __global__ void __launch_bounds__(G::NT, G::OCC) fwd_kernel(FwdArgs a) {
       for (int j = 0; j < NB; ++j) acc[i][j] = f32x16_t{};
     G::run(acc, Wt, a.d, 0, rows, (const S*)a.H, a.d, n0, (int)a.T, a.d, smem);
 
-    // Tiles past the end of a shard mask their padded rows; full tiles (all but the
-    // last of each shard) take the select-free loops.  Register r of row block i
-    // holds tile row wm + 32 i + acc_row(r, lane) = wm + 4 (lane / 32) + (a constant),
-    // so the mask compares that constant with one per-lane limit.
     const bool full = rows == BM;
     const int lim = rows - wm - 4 * (lane >> 5);
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
-      // The maximum is taken on the raw logits and scaled once: scaling by a positive
-      // constant is monotone under rounding, so this equals the maximum of the scaled
-      // values.
-      float tmax = -INFINITY;
-      if (full) {
-#pragma unroll
-        for (int i = 0; i < MB; ++i)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, acc[i][j][r]);
-      } else {
-#pragma unroll
-        for (int i = 0; i < MB; ++i)
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            if (32 * i + 8 * (r >> 2) + (r & 3) < lim) tmax = fmaxf(tmax, acc[i][j][r]);
-      }
-      tmax *= kLog2e;
-      const float scale = tmax > m_run[j] ? __builtin_amdgcn_exp2f(m_run[j] - tmax) : 1.f;
-      m_run[j] = fmaxf(m_run[j], tmax);
-      float sum = 0.f;
-      if (full) {
-#pragma unroll
-        for (int i = 0; i < MB; ++i)
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            sum += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][j][r], kLog2e, -m_run[j]));
-      } else {
-#pragma unroll
-        for (int i = 0; i < MB; ++i)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][j][r], kLog2e, -m_run[j]));
-            sum += (32 * i + 8 * (r >> 2) + (r & 3) < lim) ? e : 0.f;
-          }
-      }
-      s_run[j] = s_run[j] * scale + sum;
-
-      // Target gather: exactly one tile in the whole vocabulary holds the target.
-      const int64_t rel = tgt[j] - gid0;
-      if (rel >= 0 && rel < rows) {
-        const int relw = (int)rel - wm;
-        if (relw >= 0 && relw < G::WM) {
-          const int rib = relw & 31;
-          if (((rib >> 2) & 1) == (lane >> 5)) {
-            const int want_i = relw >> 5, want_r = (rib >> 3) * 4 + (rib & 3);
-            float yv = 0.f;
-#pragma unroll
-            for (int i = 0; i < MB; ++i)
-#pragma unroll
-              for (int r = 0; r < 16; ++r) yv = (i == want_i && r == want_r) ? acc[i][j][r] : yv;
-            a.y_tgt[n0 + wn + 32 * j + (lane & 31)] = yv;
-          }
-        }
-      }
+      fold_column<MB, NB>(acc, j, full, lim, m_run[j], s_run[j]);
+      gather_target<MB, NB>(acc, j, tgt[j] - gid0, rows, wm, lane,
+                            a.y_tgt + n0 + wn + 32 * j + (lane & 31));
     }
   }
-
-  // Merge the two lane halves that share a token column, then the wave rows.
-#pragma unroll
-  for (int j = 0; j < NB; ++j) {
-    const float mo = __shfl_xor(m_run[j], 32);
-    const float so = __shfl_xor(s_run[j], 32);
-    merge_state(m_run[j], s_run[j], mo, so);
-  }
-  __syncthreads();  // smem is free after the last tile
-  float* red = (float*)smem;  // [WGM][2][BN]
-  const int wr = wave / G::WGN;
-  if (lane < 32) {
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      red[(wr * 2) * BN + wn + 32 * j + lane] = m_run[j];
-      red[(wr * 2 + 1) * BN + wn + 32 * j + lane] = s_run[j];
-    }
-  }
-  __syncthreads();
-  if (wr == 0 && lane < 32) {
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      const int c = wn + 32 * j + lane;
-      for (int w2 = 1; w2 < G::WGM; ++w2)
-        merge_state(m_run[j], s_run[j], red[(w2 * 2) * BN + c], red[(w2 * 2 + 1) * BN + c]);
-      const int64_t n = n0 + c;
-      if (n < a.T) {
-        a.m_part[(int64_t)split * a.T + n] = m_run[j];
-        a.s_part[(int64_t)split * a.T + n] = s_run[j];
-      }
-    }
-  }
+  write_partials<G>(a, m_run, s_run, split, n0, (float*)smem);
 }
 
-// Folds the per-split partial states of each token in split order (the
-// visiting order), then finalises lse = m + log z and loss = lse - y_target.
+// The forward on small tiles (see Ring): the slices of a workgroup's whole range of
+// vocabulary tiles form one stream through the ring.  The token blocks of one vocabulary
+// range run side by side on an XCD, so that its L2 reads their W once.
+template <class E, class G>
+__global__ void __launch_bounds__(G::NT, G::OCC* G::NWAVES / 4) stream_fwd_kernel(FwdArgs a) {
+  using S = typename E::storage;
+  constexpr int BM = G::BM, BN = G::BN, MB = G::MB, NB = G::NB;
+  __shared__ __attribute__((aligned(16))) char smem[G::LDS_BYTES];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = G::wave_m(wave), wn = G::wave_n(wave);
+  const int logical = xcd_logical(blockIdx.x, gridDim.x);
+  const int split = logical / a.n_tok_blocks;
+  const int n0 = (logical % a.n_tok_blocks) * BN;
+  const int t_begin = (int)((int64_t)split * a.n_tiles / a.n_splits);
+  const int t_end = (int)((int64_t)(split + 1) * a.n_tiles / a.n_splits);
+
+  float m_run[NB], s_run[NB];
+  int64_t tgt[NB];
+#pragma unroll
+  for (int j = 0; j < NB; ++j) {
+    m_run[j] = -INFINITY;
+    s_run[j] = 0.f;
+    const int64_t n = n0 + wn + 32 * j + (lane & 31);
+    tgt[j] = n < a.T ? a.targets[n] : -1;
+  }
+  // (waited for here: from now on only slice loads, and rare stores, are in flight)
+#pragma unroll
+  for (int j = 0; j < NB; ++j) asm volatile("" : "+v"(tgt[j]));
+
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
+  const int nk = (a.d + G::BK - 1) / G::BK;
+  const int tail_chunks = a.d % G::BK ? a.d % G::BK / E::VEC : G::CPR;
+  const int total = (t_end - t_begin) * nk;
+
+  // the loading side of the stream: tile, slice and ring slot of the next slice to load
+  const char* baseB = (const char*)((const S*)a.H + (int64_t)n0 * a.d);
+  const char* baseA = nullptr;
+  uint32_t offA[G::A_LOADS], offB[G::B_LOADS];
+  G::offsets(offB, (int)min((int64_t)BN, a.T - n0), a.d, wave, lane);
+  int l_pos = 0, l_tile = t_begin, l_kt = 0, l_slot = 0, loaded = 0;
+  auto load_next = [&]() {
+    if (l_kt == 0) {
+      while (l_tile >= a.st.tile0[l_pos + 1]) ++l_pos;
+      const int r0 = (l_tile - a.st.tile0[l_pos]) * BM;
+      baseA = (const char*)((const S*)a.st.w[l_pos] + (int64_t)r0 * a.d);
+      G::offsets(offA, min(BM, a.st.rows[l_pos] - r0), a.d, wave, lane);
+    }
+    const int chunks = l_kt == nk - 1 ? tail_chunks : G::CPR;
+    const uint32_t l = lds0 + (uint32_t)(l_slot * G::SLICE_BYTES);
+    G::issue(baseA + (int64_t)l_kt * 128, offA, chunks, l, wave, lane);
+    G::issue(baseB + (int64_t)l_kt * 128, offB, chunks, l + BM * 128, wave, lane);
+    if (++l_kt == nk) {
+      l_kt = 0;
+      ++l_tile;
+    }
+    l_slot = l_slot + 1 == G::STAGES ? 0 : l_slot + 1;
+    ++loaded;
+  };
+  for (int k = 0; k < min(G::STAGES - 1, total); ++k) load_next();
+
+  f32x16_t acc[MB][NB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) acc[i][j] = f32x16_t{};
+  int pos = 0, ti = t_begin, kt = 0, slot = 0;
+  for (int it = 0; it < total; ++it) {
+    // Slice `it` has landed (loads return in order; all but the youngest STAGES - 2
+    // slices are waited for, at the end of the stream all of them), and no wave reads
+    // the slot refilled next any more.
+    if (loaded - it == G::STAGES - 1)
+      wait_vmcnt<(G::STAGES - 2) * G::NLOADS>();
+    else
+      wait_vmcnt<0>();
+    wait_lgkmcnt0();
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    if (loaded < total) load_next();
+    __builtin_amdgcn_sched_barrier(0);
+    G::multiply(acc, smem + slot * G::SLICE_BYTES, wm, wn, lane);
+    slot = slot + 1 == G::STAGES ? 0 : slot + 1;
+    if (++kt == nk) {
+      kt = 0;
+      while (ti >= a.st.tile0[pos + 1]) ++pos;
+      const int r0 = (ti - a.st.tile0[pos]) * BM;
+      const int rows = min(BM, a.st.rows[pos] - r0);
+      const int64_t gid0 = a.st.off[pos] + r0;
+      const bool full = rows == BM;
+      const int lim = rows - wm - 4 * (lane >> 5);
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        fold_column<MB, NB>(acc, j, full, lim, m_run[j], s_run[j]);
+        gather_target<MB, NB>(acc, j, tgt[j] - gid0, rows, wm, lane,
+                              a.y_tgt + n0 + wn + 32 * j + (lane & 31));
+#pragma unroll
+        for (int i = 0; i < MB; ++i) acc[i][j] = f32x16_t{};
+      }
+      ++ti;
+    }
+  }
+  write_partials<G>(a, m_run, s_run, split, n0, (float*)smem);
+}
+
+// Folds the per-split partial states of each token, then finalises lse = m + log z and loss = lse - y_target.
+template <int LPT>
 __global__ void __launch_bounds__(256) comb_kernel(CombArgs a) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t t = ((int64_t)blockIdx.x * 256 + threadIdx.x) / LPT;
   if (t >= a.T) return;
-  float m = -INFINITY, s = 0.f;
-  for (int k = 0; k < a.n_splits; ++k)
-    merge_state(m, s, a.m_part[(int64_t)k * a.T + t], a.s_part[(int64_t)k * a.T + t]);
+  float m, s;
+  merge_splits<LPT>(a.m_part, a.s_part, a.T, t, a.n_splits, m, s);
+  if (threadIdx.x % LPT) return;
   const float lse = (m + __builtin_amdgcn_logf(s)) * kLn2;
   const int64_t tg = a.targets[t];
   float loss;
@@ -605,15 +838,18 @@ __global__ void __launch_bounds__(256) state_init_kernel(float* state, int64_t T
   state[2 * T + t] = 0.f;
 }
 
-// state (m, s) <- fold of state and the shard's split partials, in split order.
+// state (m, s) <- fold of state and the shard's split partials.
+template <int LPT>
 __global__ void __launch_bounds__(256) fold_merge_kernel(FoldArgs a) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t t = ((int64_t)blockIdx.x * 256 + threadIdx.x) / LPT;
   if (t >= a.T) return;
+  float mq, sq;
+  merge_splits<LPT>(a.m_part, a.s_part, a.T, t, a.n_splits, mq, sq);
+  if (threadIdx.x % LPT) return;
   const float m_in = a.state[t];
   float m = m_in == -INFINITY ? -INFINITY : m_in * kLog2e;
   float s = a.state[a.T + t];
-  for (int k = 0; k < a.n_splits; ++k)
-    merge_state(m, s, a.m_part[(int64_t)k * a.T + t], a.s_part[(int64_t)k * a.T + t]);
+  merge_state(m, s, mq, sq);
   a.state[t] = m == -INFINITY ? -INFINITY : m * kLn2;
   a.state[a.T + t] = s;
 }
@@ -1103,6 +1339,8 @@ template <> struct Cfg<Bf16> {
   // 256 (160 x 64 per wave, 0.7 fragment reads per MFMA)
   using MmWide = GemmDma<320, 256, 2, 4>;
   using LogitsTail = GemmDma<256, 256, 2, 4, 64, 2, Bf16, true>;
+  using Stream128 = Ring<256, 128, 4, 2, 3, Bf16>;  // forward on few tokens, see fwd_tile
+  using Stream64 = Ring<128, 64, 4, 2, 6, Bf16>;
   static constexpr int KALIGN = 64;  // K granularity the dH / dW launches need
 };
 template <> struct Cfg<F32> {
@@ -1112,6 +1350,8 @@ template <> struct Cfg<F32> {
   using Mm = Logits;  // the dH / dW contractions
   using MmWide = GemmDma<320, 256, 2, 4, 64, 2, F32>;
   using LogitsTail = GemmDma<256, 256, 2, 4, 64, 2, F32, true>;
+  using Stream128 = Ring<256, 128, 4, 2, 3, F32>;
+  using Stream64 = Ring<128, 64, 4, 2, 6, F32>;
   static constexpr int KALIGN = 32;  // K granularity the dH / dW launches need
 };
 
@@ -1123,8 +1363,18 @@ static bool launch_fwd_g(const FwdArgs& a, hipStream_t s) {
   hipLaunchKernelGGL((fwd_kernel<E, G>), dim3(grid), dim3(G::NT), 0, s, a);
   return launched_ok();
 }
+template <class E, class G>
+static bool launch_stream(const FwdArgs& a, hipStream_t s) {
+  const unsigned grid = (unsigned)(a.n_tok_blocks * a.n_splits);
+  hipLaunchKernelGGL((stream_fwd_kernel<E, G>), dim3(grid), dim3(G::NT), 0, s, a);
+  return launched_ok();
+}
 template <class E>
 static bool launch_fwd(const FwdArgs& a, hipStream_t s) {
+  switch (a.kind) {
+    case 1: return launch_stream<E, typename Cfg<E>::Stream128>(a, s);
+    case 2: return launch_stream<E, typename Cfg<E>::Stream64>(a, s);
+  }
   if (a.d % E::KB == 0) return launch_fwd_g<E, typename Cfg<E>::Logits>(a, s);
   return launch_fwd_g<E, typename Cfg<E>::LogitsTail>(a, s);
 }
@@ -1239,6 +1489,26 @@ TileShape tile_shape(int dtype) {
   return t;
 }
 
+// Microseconds a workgroup takes per 128-byte slice of one tile, measured on launches
+// that fill the chip: with two or more token blocks sharing W in the L2s, and with one
+// block, where W streams from memory (bfloat16, d = 4096 and 1000, T = 40..1024; float32
+// is bound by its matrix rate either way, d = 2880).
+template <class E>
+static FwdTile fwd_tile_of(int kind) {
+  constexpr bool b16 = sizeof(typename E::storage) == 2;
+  using G0 = typename Cfg<E>::Logits;
+  using G1 = typename Cfg<E>::Stream128;
+  using G2 = typename Cfg<E>::Stream64;
+  switch (kind) {
+    case 1: return b16 ? FwdTile{G1::BM, G1::BN, G1::OCC, 1.4, 1.5} : FwdTile{G1::BM, G1::BN, G1::OCC, 4.44, 4.44};
+    case 2: return b16 ? FwdTile{G2::BM, G2::BN, G2::OCC, 0.47, 0.5} : FwdTile{G2::BM, G2::BN, G2::OCC, 1.33, 1.36};
+  }
+  return b16 ? FwdTile{G0::BM, G0::BN, G0::OCC, 1.4, 1.8} : FwdTile{G0::BM, G0::BN, G0::OCC, 7.45, 7.45};
+}
+FwdTile fwd_tile(int dtype, int kind) {
+  return dtype == 1 ? fwd_tile_of<Bf16>(kind) : fwd_tile_of<F32>(kind);
+}
+
 bool run_ws_init(unsigned long long* counter, hipStream_t s) {
   hipLaunchKernelGGL(ws_init_kernel, dim3(1), dim3(64), 0, s, counter);
   return launched_ok();
@@ -1253,8 +1523,10 @@ bool run_fwd(int dtype, const FwdArgs& a, hipStream_t s) {
   return dtype == 1 ? launch_fwd<Bf16>(a, s) : launch_fwd<F32>(a, s);
 }
 bool run_comb(const CombArgs& a, hipStream_t s) {
-  const unsigned grid = (unsigned)((a.T + 255) / 256);
-  hipLaunchKernelGGL(comb_kernel, dim3(grid), dim3(256), 0, s, a);
+  if (a.n_splits >= kManySplits)
+    hipLaunchKernelGGL(comb_kernel<16>, dim3((unsigned)((a.T + 15) / 16)), dim3(256), 0, s, a);
+  else
+    hipLaunchKernelGGL(comb_kernel<1>, dim3((unsigned)((a.T + 255) / 256)), dim3(256), 0, s, a);
   return launched_ok();
 }
 bool run_state_init(float* state, int64_t T, hipStream_t s) {
@@ -1264,7 +1536,10 @@ bool run_state_init(float* state, int64_t T, hipStream_t s) {
 }
 bool run_fold_merge(const FoldArgs& a, hipStream_t s) {
   if (a.T <= 0) return true;
-  hipLaunchKernelGGL(fold_merge_kernel, dim3((unsigned)((a.T + 255) / 256)), dim3(256), 0, s, a);
+  if (a.n_splits >= kManySplits)
+    hipLaunchKernelGGL(fold_merge_kernel<16>, dim3((unsigned)((a.T + 15) / 16)), dim3(256), 0, s, a);
+  else
+    hipLaunchKernelGGL(fold_merge_kernel<1>, dim3((unsigned)((a.T + 255) / 256)), dim3(256), 0, s, a);
   return launched_ok();
 }
 bool run_fold_finalize(const FinArgs& a, hipStream_t s) {
