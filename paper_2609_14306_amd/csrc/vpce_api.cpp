@@ -253,6 +253,231 @@ std::vector<Chunk> strip_chunks(const vp_problem* prob, const StripPlan& plan) {
   return chunks;
 }
 
+// The backward on few tokens (one token chunk of at most kFewBwdTokens): strips of one
+// or several shards, dH split into jobs along the vocabulary (see few_stage_kernel).
+// Everything is laid out in the workspace that strip_plan asks for; without H^T and
+// W^T in it there is room for partial dH sums and for longer strips.
+constexpr int64_t kFewBwdTokens = 2048;
+struct FewStrip {
+  struct Seg {
+    int q;
+    int64_t v0, rows, row0;
+  };
+  std::vector<Seg> segs;
+  std::vector<vpce::FewJob> jobs;
+  int64_t rows_pad = 0;
+};
+struct FewPlan {
+  int cls = -1;
+  int64_t Tc = 0, Vr = 0;
+  int max_jobs = 1;
+  size_t off_g[2], off_gt[2], off_part, off_yt;
+  double time = 0;
+  std::vector<FewStrip> strips;
+};
+
+// Plan for one tile class; false if the workspace has no room for it.
+bool few_plan_cls(const vp_problem* p, size_t total, int cls, FewPlan* out) {
+  const vpce::FewTile ft = vpce::few_tile(p->dtype, cls);
+  const int64_t eb = (int64_t)elem_bytes(p->dtype), KB = vpce::tile_shape(p->dtype).kblock;
+  const int64_t T = p->T, d = p->d, slot = T * d * 4;
+  const int64_t budget = p->strip_elems > 0 ? p->strip_elems : kDefaultStrip;
+  FewPlan f;
+  f.cls = cls;
+  f.Tc = round_up(T, ft.bn);
+  const int64_t avail = (int64_t)total - (int64_t)kHeaderBytes - (int64_t)align256((size_t)T * 4) - 5 * 256;
+  // at most a quarter of the workspace for partial sums, the rest for the strips
+  const int64_t slots = std::max<int64_t>(1, std::min<int64_t>(avail / 4 / slot, vpce::kMaxJobs));
+  const int64_t room = avail - (slots > 1 ? slots * slot : 0);
+  const int64_t cap = round_down(std::min(budget / f.Tc, room / (4 * f.Tc * eb)), ft.bm);
+  if (cap < ft.bm) return false;
+
+  // Strips: a shard above the cap is cut into balanced pieces, a strip each; smaller
+  // shards share a strip while they fit.  A shard of less than 256 rows keeps a strip
+  // of its own (beside others it would be padding for the most part).
+  for (int i = 0; i < p->P; ++i) {
+    const int q = p->order ? p->order[i] : i;
+    const int64_t Vq = p->shard_rows[q];
+    if (Vq == 0) continue;
+    const int64_t pad = round_up(Vq, ft.bm);
+    if (pad <= cap) {
+      const bool join = !f.strips.empty() && f.strips.back().rows_pad + pad <= cap && Vq >= 256 &&
+                        f.strips.back().segs.back().rows >= 256 &&
+                        f.strips.back().segs.back().rows == p->shard_rows[f.strips.back().segs.back().q] &&
+                        (int64_t)f.strips.back().segs.size() < std::min<int64_t>(slots, vpce::kMaxSegs);
+      if (!join) f.strips.emplace_back();
+      f.strips.back().segs.push_back({q, 0, Vq, f.strips.back().rows_pad});
+      f.strips.back().rows_pad += pad;
+      continue;
+    }
+    const int64_t vc = round_up(ceil_div(Vq, ceil_div(Vq, cap)), ft.bm);
+    for (int64_t v0 = 0; v0 < Vq; v0 += vc) {
+      const int64_t rows = std::min(vc, Vq - v0);
+      f.strips.emplace_back();
+      f.strips.back().segs.push_back({q, v0, rows, 0});
+      f.strips.back().rows_pad = round_up(rows, ft.bm);
+    }
+  }
+  for (const FewStrip& st : f.strips) f.Vr = std::max(f.Vr, st.rows_pad);
+
+  // Jobs: a dH tile's sum should take no longer than half of what its launch gives a CU
+  // to do, counted in slices of all its tiles (and no less than eight slices).
+  const int64_t n_tb = ceil_div(T, ft.bn), n_nb = ceil_div(d, ft.bm);
+  const int64_t n = (int64_t)f.strips.size();
+  auto res_slices = [&](const FewStrip& st) { return st.rows_pad / ft.bm * n_tb * ceil_div(d, KB); };
+  std::vector<bool> used(vpce::kMaxJobs, false);
+  f.time = ft.us * ((double)res_slices(f.strips[0]) / kCUs + 0.5 * ceil_div(d, KB));
+  for (int64_t k = 0; k < n; ++k) {
+    FewStrip& st = f.strips[k];
+    int64_t ks = 0;
+    for (const FewStrip::Seg& sg : st.segs) ks += ceil_div(sg.rows, KB);
+    const int64_t work = n_tb * n_nb * ks + ceil_div(st.rows_pad, ft.bn) * n_nb * ceil_div(T, KB) +
+                         (k + 1 < n ? res_slices(f.strips[k + 1]) : 0);
+    int64_t target = std::max<int64_t>(8, work / kCUs / 2);
+    for (;; target += target / 4) {
+      int64_t jobs = 0;
+      for (const FewStrip::Seg& sg : st.segs) jobs += ceil_div(ceil_div(sg.rows, KB), target);
+      if (jobs <= std::max<int64_t>(slots, (int64_t)st.segs.size())) break;
+    }
+    int64_t longest = std::max(ceil_div(d, KB), ceil_div(T, KB));
+    for (size_t i = 0; i < st.segs.size(); ++i) {
+      const int64_t blocks = ceil_div(st.segs[i].rows, KB);
+      const int64_t per = ceil_div(blocks, ceil_div(blocks, target));
+      for (int64_t b = 0; b < blocks; b += per) {
+        const size_t j = st.jobs.size();
+        st.jobs.push_back({(int32_t)i, (int32_t)(b * KB),
+                           (int32_t)(std::min(st.segs[i].rows, (b + per) * KB) - b * KB), used[j] ? 1 : 0});
+        used[j] = true;
+      }
+      longest = std::max(longest, per);
+    }
+    f.max_jobs = std::max(f.max_jobs, (int)st.jobs.size());
+    f.time += ft.us * ((double)work / kCUs + 0.5 * longest);
+  }
+
+  const size_t strip = align256((size_t)(f.Vr * f.Tc * eb));
+  size_t off = kHeaderBytes;
+  for (int b = 0; b < 2; ++b) {
+    f.off_g[b] = off;
+    f.off_gt[b] = off + strip;
+    off += 2 * strip;
+  }
+  f.off_part = off;
+  if (f.max_jobs > 1) off += align256((size_t)(f.max_jobs * slot));
+  f.off_yt = off;
+  if (off + align256((size_t)T * 4) > total) return false;
+  *out = std::move(f);
+  return true;
+}
+
+// The plan of the class with the shorter estimated time; false for problems that run
+// the general backward (more tokens than kFewBwdTokens, several token chunks, or a
+// strip budget too small for one tile).
+bool few_plan(const vp_problem* p, FewPlan* out) {
+  if (p->T == 0 || p->T > kFewBwdTokens) return false;
+  const StripPlan s = strip_plan(p);
+  if (s.Tc < p->T) return false;
+  bool found = false;
+  for (int cls = 0; cls < 2; ++cls) {
+    FewPlan f;
+    if (few_plan_cls(p, s.total, cls, &f) && (!found || f.time < out->time)) {
+      *out = std::move(f);
+      found = true;
+    }
+  }
+  return found;
+}
+
+vp_status backward_few(const vp_problem* p, const FewPlan& f, int64_t V, const void* H,
+                       const void* const* W_shards, const int64_t* targets, const float* lse,
+                       const float* grad_loss, float* dH, float* const* dW_shards, void* ws,
+                       hipStream_t s) {
+  const int64_t T = p->T, d = p->d;
+  const size_t eb = elem_bytes(p->dtype);
+  const vpce::FewTile ft = vpce::few_tile(p->dtype, f.cls);
+  char* wsb = (char*)ws;
+  float* yt = (float*)(wsb + f.off_yt);
+  float* part = f.max_jobs > 1 ? (float*)(wsb + f.off_part) : dH;
+
+  vpce::TgtArgs ta;
+  memset(&ta, 0, sizeof(ta));
+  int32_t n_tiles = 0;
+  build_table(p, W_shards, ft.bm, &ta.st, &n_tiles);
+  ta.H = H;
+  ta.targets = targets;
+  ta.T = T;
+  ta.V = V;
+  ta.d = (int32_t)d;
+  ta.yt = yt;
+  ta.count = (unsigned long long*)ws;
+  ta.ignore_index = p->ignore_index;
+  if (!vpce::run_target_logits(p->dtype, ta, s)) return VP_ERR_HIP;
+
+  int64_t off[VP_MAX_SHARDS];
+  int64_t acc = 0;
+  for (int q = 0; q < p->P; ++q) {
+    off[q] = acc;
+    acc += p->shard_rows[q];
+  }
+  auto segments = [&](const FewStrip& st, vpce::FewSeg* out) {
+    for (size_t i = 0; i < st.segs.size(); ++i) {
+      const FewStrip::Seg& sg = st.segs[i];
+      out[i].w = (const char*)W_shards[sg.q] + (size_t)(sg.v0 * d) * eb;
+      out[i].dw = dW_shards[sg.q] + sg.v0 * d;
+      out[i].gid0 = off[sg.q] + sg.v0;
+      out[i].rows = (int32_t)sg.rows;
+      out[i].row0 = (int32_t)sg.row0;
+    }
+    return (int32_t)st.segs.size();
+  };
+  // Launch k writes the residual of strip k (into buffer k % 2) and contracts strip
+  // k - 1 (from the other one), as the general backward does.
+  const int64_t n = (int64_t)f.strips.size(), KB = vpce::tile_shape(p->dtype).kblock;
+  for (int64_t k = 0; k <= n; ++k) {
+    vpce::FewArgs a;
+    memset(&a, 0, sizeof(a));
+    a.g.H = H;
+    a.g.targets = targets;
+    a.g.lse = lse;
+    a.g.grad = grad_loss;
+    a.g.strip = wsb + f.off_g[k % 2];
+    a.g.strip_t = wsb + f.off_gt[k % 2];
+    a.g.Tc = f.Tc;
+    a.g.Vc = f.Vr;
+    a.g.V = V;
+    a.g.ignore_index = p->ignore_index;
+    a.g.yt = yt;
+    a.g.N = (int32_t)T;
+    a.g.d = (int32_t)d;
+    if (k < n) {
+      a.n_gseg = segments(f.strips[k], a.gseg);
+      a.g_tiles = (int32_t)(f.strips[k].rows_pad / ft.bm);
+    }
+    int64_t longest = 0;
+    if (k >= 1) {
+      const FewStrip& st = f.strips[k - 1];
+      a.n_cseg = segments(st, a.cseg);
+      a.n_job = (int32_t)st.jobs.size();
+      for (size_t j = 0; j < st.jobs.size(); ++j) {
+        a.job[j] = st.jobs[j];
+        longest = std::max<int64_t>(longest, ceil_div(st.jobs[j].rows, KB));
+      }
+      a.w_tiles = (int32_t)ceil_div(st.rows_pad, ft.bn);
+      a.G = wsb + f.off_g[(k - 1) % 2];
+      a.Gt = wsb + f.off_gt[(k - 1) % 2];
+      a.part = part;
+      a.beta_w = (p->flags & VP_ACCUMULATE_DW) != 0;
+    }
+    // the kinds with the longest sums first, so that the last round of tiles is short
+    const int64_t slices[3] = {longest, ceil_div(T, KB), ceil_div(d, KB)};
+    for (int i = 0; i < 3; ++i) a.order[i] = i;
+    std::sort(a.order, a.order + 3, [&](int x, int y) { return slices[x] > slices[y]; });
+    if (!vpce::run_few_stage(p->dtype, f.cls, a, s)) return VP_ERR_HIP;
+  }
+  if (f.max_jobs > 1 && !vpce::run_sum_parts(part, f.max_jobs, T * d, dH, s)) return VP_ERR_HIP;
+  return VP_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -478,6 +703,14 @@ vp_status vp_ce_plan_info(const vp_problem* prob, vp_plan_info* info) {
   const vp_status st = validate(prob, nullptr);
   if (st != VP_OK) return st;
   if (!info) return VP_ERR_NULL;
+  FewPlan few;
+  if (few_plan(prob, &few)) {
+    info->Tc = few.Tc;
+    info->Vc = few.Vr;
+    info->strips = (int64_t)few.strips.size();
+    info->stage_launches = info->strips + 1;
+    return VP_OK;
+  }
   const StripPlan plan = strip_plan(prob);
   const int64_t n = prob->T > 0 ? (int64_t)strip_chunks(prob, plan).size() : 0;
   info->Tc = plan.Tc;
@@ -509,6 +742,9 @@ vp_status vp_ce_backward(const vp_problem* prob, const void* H, const void* cons
     if (misaligned(H) || misaligned(dH)) return VP_ERR_ALIGN;
   }
   hipStream_t s = (hipStream_t)stream;
+  FewPlan few;
+  if (few_plan(prob, &few))
+    return backward_few(prob, few, V, H, W_shards, targets, lse, grad_loss, dH, dW_shards, ws, s);
   unsigned long long* counter = (unsigned long long*)ws;
   if (!vpce::run_ws_init(counter, s)) return VP_ERR_HIP;
   const bool accumulate = (prob->flags & VP_ACCUMULATE_DW) != 0;

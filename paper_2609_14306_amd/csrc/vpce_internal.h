@@ -97,6 +97,10 @@ struct TgtArgs {
   int64_t T, V;
   int32_t d;
   float* yt;
+  // when not null: set to the number of targets outside [0, V) that are not ignore_index
+  // (counted by one workgroup: for few tokens)
+  unsigned long long* count;
+  int64_t ignore_index;
 };
 
 // C[M][N] = (beta ? C : 0) + A B^T with A [M][K] (row stride lda) and B [N][K]
@@ -135,6 +139,41 @@ struct TileShape {
 };
 
 TileShape tile_shape(int dtype);
+
+// The backward on few tokens (at most one token chunk): a strip holds whole shards, or
+// one balanced piece of a large shard, and the dH tiles split its vocabulary rows into
+// jobs, each summing into a partial dH of its own.
+constexpr int kMaxSegs = 16, kMaxJobs = 32;
+struct FewSeg {  // one shard (piece) of a strip, in visiting order
+  const void* w;   // its first row, [rows, d]
+  float* dw;
+  int64_t gid0;    // global id of the first row
+  int32_t rows, row0;  // rows, and the strip row that the first of them has
+};
+struct FewJob {  // rows k0 .. k0 + rows - 1 of a segment (k0 in whole k-blocks)
+  int32_t seg, k0, rows, beta;
+};
+struct FewArgs {
+  GradArgs g;  // residual tiles; W, gid0, M are the segments'
+  FewSeg gseg[kMaxSegs], cseg[kMaxSegs];  // of the strip written and of the one contracted
+  FewJob job[kMaxJobs];
+  int32_t n_gseg, n_cseg, n_job;
+  int32_t g_tiles, w_tiles;  // residual row tiles of the strip written, dW ones of the other
+  int32_t order[3];          // kinds (0 dH, 1 dW, 2 residual) in launch order
+  int32_t beta_w;            // dW is added to
+  const void *G, *Gt;        // residual of the strip contracted
+  float* part;               // [jobs][T][d], or dH itself for one job
+};
+// tile class 0: 256 x 256 tiles; 1: 128 x 64 ones
+struct FewTile {
+  int bm, bn;   // residual tile: vocabulary rows by tokens; the contractions' tiles are
+                // bm columns of d by bn rows
+  double us;    // time per 128-byte slice of a tile, a CU to itself
+};
+FewTile few_tile(int dtype, int cls);
+bool run_few_stage(int dtype, int cls, const FewArgs& a, hipStream_t s);
+// out[i] = sum over k < n of part[k * len + i], in the order of k; len % 4 == 0
+bool run_sum_parts(const float* part, int n, int64_t len, float* out, hipStream_t s);
 
 // Tiles the forward can run on: kind 0 is the 256 x 256 tile of every large problem,
 // the others are the streamed tiles for few tokens.

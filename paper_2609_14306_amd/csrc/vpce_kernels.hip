@@ -142,10 +142,70 @@ __device__ __forceinline__ void lds_dma16_lane(const void* addr, uint32_t l0) {
                : "memory");
 }
 
+// An operand whose contraction index is its row index, read transposed from LDS: a
+// slice is E::KB rows (k) of COLS values (n, the tile's rows of C^T), copied row by row
+// by the direct-to-LDS loads.  bfloat16 fragments come from gfx950's LDS transpose read
+// (ds_read_b64_tr_b16: in each group of 16 lanes, lane a supplies the four values at its
+// address, and lane i receives value i % 4 of lanes i / 4, 4 + i / 4, 8 + i / 4 and
+// 12 + i / 4, i.e. a 4 x 16 block transposed), two per 8-value fragment; float32 ones
+// from four 4-byte reads.  The 16-byte chunks of k-row r are swizzled by swz(r) so that
+// the rows that one read touches lie in different banks.
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
+template <class E, int COLS, int NWAVES>
+struct TrOperand {
+  using S = typename E::storage;
+  using F16 = typename E::frag16;
+  static constexpr int ROW_BYTES = COLS * (int)sizeof(S);
+  static constexpr int CPR = ROW_BYTES / 16, RPL = 1024 / ROW_BYTES;  // k-rows per load
+  static_assert(ROW_BYTES >= 256 && ROW_BYTES <= 1024, "the swizzle needs two or four bank groups");
+  __device__ __forceinline__ static int swz(int k) {
+    return sizeof(S) == 2 ? 4 * (k & 3) : 8 * ((k >> 2) & 1);
+  }
+  __device__ __forceinline__ static int row(int q, int wave, int lane) {
+    return (wave + q * NWAVES) * RPL + lane / CPR;
+  }
+  // Byte offset, from the slice's first row, of the chunk that this lane loads with
+  // load q: k-row min(row, last), column chunk clamped to the last one below `cols`
+  // (columns past it feed rows of C^T that are never stored; k-rows past `last` meet
+  // zeros of the other operand).
+  __device__ __forceinline__ static uint32_t offset(int q, int wave, int lane, int64_t ld, int cols,
+                                                    int last) {
+    const int r = row(q, wave, lane), c = (lane % CPR) ^ swz(r);
+    return (uint32_t)(min(r, last) * ld * (int64_t)sizeof(S)) + 16u * (uint32_t)min(c, cols / E::VEC - 1);
+  }
+  // Lane's byte offset of the fragment of 32-wide block n0 at sub-step 0, and the read.
+  __device__ __forceinline__ static uint32_t frag_offset(int n0, int lane) {
+    if constexpr (sizeof(S) == 2) {
+      const int k = 8 * (lane >> 5) + ((lane & 15) >> 2);
+      const int n = n0 + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+      return (uint32_t)(k * ROW_BYTES + (((n >> 3) ^ swz(k)) << 4) + (n & 7) * 2);
+    } else {
+      const int k = 4 * (lane >> 5), n = n0 + (lane & 31);
+      return (uint32_t)(k * ROW_BYTES + (((n >> 2) ^ swz(k)) << 4) + (n & 3) * 4);
+    }
+  }
+  __device__ __forceinline__ static F16 frag(const char* p, int kk) {
+    if constexpr (sizeof(S) == 2) {
+      using P = __attribute__((address_space(3))) s16x4_t*;
+      typedef short s16x8_t __attribute__((ext_vector_type(8)));
+      const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((P)(p + kk * 16 * ROW_BYTES));
+      const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((P)(p + (kk * 16 + 4) * ROW_BYTES));
+      return __builtin_bit_cast(F16, (s16x8_t)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    } else {
+      F16 f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) f[e] = *(const float*)(p + (kk * 8 + e) * ROW_BYTES);
+      return f;
+    }
+  }
+};
+
 // KTAIL_: K may be any number of whole 16-byte chunks; otherwise it is a multiple of
 // the slice depth.
+// ATR_: A is [K][lda] with its rows along the contraction, read transposed (TrOperand);
+// K is its number of rows, any number, and B is whole slices that hold zeros past K.
 template <int BM_, int BN_, int WGM_, int WGN_, int BK_ = 64, int STAGES_ = 2, class E = Bf16,
-          bool KTAIL_ = false>
+          bool KTAIL_ = false, bool ATR_ = false>
 struct GemmDma {
   using S = typename E::storage;
   using F16 = typename E::frag16;
@@ -162,7 +222,7 @@ struct GemmDma {
   static constexpr int BK = ROW_BYTES / (int)sizeof(S);  // k values per slice
   static_assert((BK_ == 32 || BK_ == 64) && STAGES >= 2, "slice depth and ring slots");
   static_assert(E::KB % BK == 0, "slices never straddle a k-block of the layout");
-  static constexpr bool KTAIL = KTAIL_;
+  static constexpr bool KTAIL = KTAIL_, ATR = ATR_;
   static constexpr int NKK = ROW_BYTES / 32;      // sub-steps per slice (two 16-byte chunks each)
   static_assert(NKK % 2 == 0, "register sets alternate per sub-step across slices");
   static constexpr int CPR = ROW_BYTES / 16;      // 16-byte chunks per row
@@ -172,6 +232,7 @@ struct GemmDma {
   static constexpr int A_LOADS = BM / RPI / NWAVES;  // load instructions per wave and slice
   static constexpr int B_LOADS = BN / RPI / NWAVES;
   static_assert(BM % (RPI * NWAVES) == 0 && BN % (RPI * NWAVES) == 0, "whole load groups per wave");
+  using TrA = TrOperand<E, BM, NWAVES>;
   static constexpr int NLOADS = A_LOADS + B_LOADS;  // per wave and slice
   // the loads of a slice go out in two halves, the larger first
   static constexpr int HALF0 = (NLOADS + 1) / 2, HALF1 = NLOADS - HALF0;
@@ -201,7 +262,10 @@ struct GemmDma {
     const char* baseA;  // byte address of the tile's first A row (k = 0)
     const char* baseB;
     int64_t kblkA, kblkB;  // elements between consecutive k-blocks (E::KB wide)
-    int tail_kt, tail_chunks;  // KTAIL: the slice that reaches past K and its live chunks
+    // KTAIL: the slice that reaches past K and its live chunks; ATR: that slice and its
+    // live rows, A's row pitch and live columns
+    int tail_kt, tail_chunks, tail_rows, colsA;
+    int64_t ldA;
     uint32_t offA[A_LOADS], offB[B_LOADS];  // per-lane byte offsets from the bases
   };
 
@@ -209,11 +273,18 @@ struct GemmDma {
                                               int m0, int M, const S* __restrict__ B, int64_t ldb,
                                               int n0, int N, int wave, int lane) {
     const int ma = min(m0, M - 1), nb = min(n0, N - 1);
-    L.baseA = (const char*)(A + (int64_t)ma * lda);
+    if constexpr (ATR)
+      L.baseA = (const char*)(A + m0);
+    else
+      L.baseA = (const char*)(A + (int64_t)ma * lda);
     L.baseB = (const char*)(B + (int64_t)nb * ldb);
     const int row_in = lane / CPR;
 #pragma unroll
     for (int q = 0; q < A_LOADS; ++q) {
+      if constexpr (ATR) {
+        L.offA[q] = TrA::offset(q, wave, lane, lda, M - m0, BK - 1);
+        continue;
+      }
       const int r = (wave + q * NWAVES) * RPI + row_in;
       const int c = (lane % CPR) ^ key(r);
       L.offA[q] = (uint32_t)((min(m0 + r, M - 1) - ma) * lda * (int64_t)sizeof(S)) + 16u * c;
@@ -242,6 +313,13 @@ struct GemmDma {
                             : L.baseB + (k0 / KB) * L.kblkB * (int64_t)sizeof(S) + L.offB[q < A_LOADS ? 0 : q - A_LOADS];
         static_assert(BK == KB, "the tail slice starts at a k-block");
         lds_dma16_lane(c < L.tail_chunks ? (const void*)p : (const void*)&zero_chunk, l);
+        return;
+      }
+    }
+    if constexpr (ATR) {
+      if (q < A_LOADS && kt == L.tail_kt) {
+        const uint32_t o = TrA::offset(q, wave, (int)(threadIdx.x & 63), L.ldA, L.colsA, L.tail_rows - 1);
+        lds_dma16_lane(L.baseA + (k0 / KB) * L.kblkA * (int64_t)sizeof(S) + o, l);
         return;
       }
     }
@@ -294,7 +372,7 @@ struct GemmDma {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave_m(wave), wn = wave_n(wave);
-    const int nk = KTAIL ? (K + BK - 1) / BK : K / BK;
+    const int nk = KTAIL || ATR ? (K + BK - 1) / BK : K / BK;
     if (nk <= 0) return;
     // row blocks of A with live rows (wave-uniform); MB unless RAGGED
     const int mb_live = RAGGED ? max(0, min(MB, (M - m0 - wm + 31) / 32)) : MB;
@@ -307,6 +385,22 @@ struct GemmDma {
       L.tail_kt = K % BK ? nk - 1 : -1;
       L.tail_chunks = K % BK / E::VEC;
     }
+    uint32_t fragA[MB];  // ATR: this lane's offsets of its A fragments
+    if constexpr (ATR) {
+      L.tail_kt = K % BK ? nk - 1 : -1;
+      L.tail_rows = K % BK;
+      L.kblkA = BK * lda;
+      L.ldA = lda;
+      L.colsA = M - m0;
+#pragma unroll
+      for (int i = 0; i < MB; ++i) fragA[i] = TrA::frag_offset(wm + 32 * i, lane);
+    }
+    auto read_a = [&](const char* slot, int kk, int i) -> F16 {
+      if constexpr (ATR)
+        return TrA::frag(slot + fragA[i], kk);
+      else
+        return read_one(slot, wm, wn, kk, lane, i);
+    };
     // prologue: the first min(STAGES, nk) slices, whole; wait for slice 0
     const int pro = min(STAGES, nk);
     for (int kt = 0; kt < pro; ++kt)
@@ -323,11 +417,10 @@ struct GemmDma {
     F16 a[MB], b[2][NB];
 #pragma unroll
     for (int idx = 0; idx < NR; ++idx) {
-      const F16 f = read_one(ring, wm, wn, 0, lane, idx);
       if (idx < MB)
-        a[idx] = f;
+        a[idx] = read_a(ring, 0, idx);
       else
-        b[0][idx - MB] = f;
+        b[0][idx - MB] = read_one(ring, wm, wn, 0, lane, idx);
     }
     for (int kt = 0; kt < nk; ++kt) {
 #pragma unroll
@@ -369,7 +462,7 @@ struct GemmDma {
           if (live) acc[i][j] = E::mma16(a[i], b[cur][j], acc[i][j]);
           __builtin_amdgcn_sched_barrier(0);
           if (idx < NB) b[cur ^ 1][idx] = read_one(src, wm, wn, skk, lane, MB + idx);
-          if (jj == NB - 1 && live) a[i] = read_one(src, wm, wn, skk, lane, i);
+          if (jj == NB - 1 && live) a[i] = read_a(src, skk, i);
           if ((idx & 1) == 0 && idx / 2 < dn && (kk == NKK - 1 || kk == 0) && dvalid)
             issue_one(L, dslice, dq0 + idx / 2, lds0, wave);
           __builtin_amdgcn_sched_barrier(0);
@@ -391,7 +484,8 @@ struct GemmDma {
 // (wait, barrier, refill, multiply).  What bounds these problems is the stream of W
 // from memory: a CU keeps (STAGES - 1) slices of it in flight, and the ring runs on
 // across tile boundaries (stream_fwd), so that no tile starts on an empty pipe.
-template <int BM_, int BN_, int WGM_, int WGN_, int STAGES_, class E>
+// ATR_: A is read transposed, as in GemmDma.
+template <int BM_, int BN_, int WGM_, int WGN_, int STAGES_, class E, bool ATR_ = false>
 struct Ring {
   using S = typename E::storage;
   using F16 = typename E::frag16;
@@ -406,6 +500,9 @@ struct Ring {
   static constexpr int A_LOADS = BM / 8 / NWAVES, B_LOADS = BN / 8 / NWAVES;
   static_assert(BM % (8 * NWAVES) == 0 && BN % (8 * NWAVES) == 0, "whole load groups per wave");
   static constexpr int NLOADS = A_LOADS + B_LOADS;
+  static constexpr bool ATR = ATR_;
+  static constexpr int LDS_ELEMS = LDS_BYTES / (int)sizeof(S);
+  using TrA = TrOperand<E, BM, NWAVES>;
   static_assert(STAGES >= 3 && (STAGES - 2) * NLOADS < 64 && LDS_BYTES <= 160 * 1024, "ring");
   static_assert(2 * WGM * BN * 4 <= LDS_BYTES, "write_partials' exchange");
 
@@ -451,7 +548,10 @@ struct Ring {
 #pragma unroll
       for (int i = 0; i < MB; ++i) {
         const int r = wm + 32 * i + (lane & 31);
-        fa[i] = *(const F16*)(slot + r * 128 + ((chunk ^ key(r)) << 4));
+        if constexpr (ATR)
+          fa[i] = TrA::frag(slot + TrA::frag_offset(wm + 32 * i, lane), kk);
+        else
+          fa[i] = *(const F16*)(slot + r * 128 + ((chunk ^ key(r)) << 4));
       }
 #pragma unroll
       for (int j = 0; j < NB; ++j) {
@@ -463,6 +563,68 @@ struct Ring {
 #pragma unroll
         for (int j = 0; j < NB; ++j) acc[i][j] = E::mma16(fa[i], fb[j], acc[i][j]);
     }
+  }
+
+  // One tile of its own (the interface of GemmDma::run): acc += A B^T.  A part slice at
+  // the end reads zeros past K, or, with ATR, repeats A's last row against B's zeros.
+  template <bool RAGGED = false>
+  __device__ __forceinline__ static void run(f32x16_t (&acc)[MB][NB], const S* __restrict__ A,
+                                             int64_t lda, int m0, int M, const S* __restrict__ B,
+                                             int64_t ldb, int n0, int N, int K, S* smem,
+                                             int64_t kblka = E::KB, int64_t kblkb = E::KB) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave_m(wave), wn = wave_n(wave);
+    const int nk = (K + BK - 1) / BK, tail = K % BK;
+    if (nk <= 0) return;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) S*)smem;
+    const char* baseA = (const char*)(ATR ? A + m0 : A + (int64_t)m0 * lda);
+    const char* baseB = (const char*)(B + (int64_t)n0 * ldb);
+    const int64_t stepA = (ATR ? BK * lda : kblka) * (int64_t)sizeof(S);
+    const int64_t stepB = kblkb * (int64_t)sizeof(S);
+    uint32_t offA[A_LOADS], offB[B_LOADS];
+    if constexpr (ATR) {
+#pragma unroll
+      for (int q = 0; q < A_LOADS; ++q) offA[q] = TrA::offset(q, wave, lane, lda, M - m0, BK - 1);
+    } else {
+      offsets(offA, M - m0, lda, wave, lane);
+    }
+    offsets(offB, N - n0, ldb, wave, lane);
+    int loaded = 0, l_slot = 0, slot = 0;
+    auto load_next = [&]() {
+      const uint32_t l = lds0 + (uint32_t)(l_slot * SLICE_BYTES);
+      const bool part = tail != 0 && loaded == nk - 1;
+      if (ATR && part) {
+#pragma unroll
+        for (int q = 0; q < A_LOADS; ++q)
+          lds_dma16_lane(baseA + TrA::offset(q, wave, lane, lda, M - m0, tail - 1),
+                         l + (uint32_t)(wave + q * NWAVES) * 1024u);
+      } else {
+        issue(baseA, offA, part ? tail / E::VEC : CPR, l, wave, lane);
+      }
+      issue(baseB, offB, part && !ATR ? tail / E::VEC : CPR, l + BM * 128, wave, lane);
+      baseA += stepA;
+      baseB += stepB;
+      l_slot = l_slot + 1 == STAGES ? 0 : l_slot + 1;
+      ++loaded;
+    };
+    for (int k = 0; k < min(STAGES - 1, nk); ++k) load_next();
+    for (int it = 0; it < nk; ++it) {  // (the waits of stream_fwd_kernel)
+      if (loaded - it == STAGES - 1)
+        wait_vmcnt<(STAGES - 2) * NLOADS>();
+      else
+        wait_vmcnt<0>();
+      wait_lgkmcnt0();
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      if (loaded < nk) load_next();
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(acc, (const char*)smem + slot * SLICE_BYTES, wm, wn, lane);
+      slot = slot + 1 == STAGES ? 0 : slot + 1;
+    }
+    wait_lgkmcnt0();
+    __builtin_amdgcn_s_barrier();
   }
 };
 
@@ -874,29 +1036,30 @@ __global__ void __launch_bounds__(256) fold_finalize_kernel(FinArgs a) {
   a.loss[t] = loss;
 }
 
-// Byte offset of element (row, col) of a 256 x 256 bfloat16 tile staged in LDS as
-// four 64-column blocks of 256 rows x 128 bytes, the 16-byte chunks of each row
+// Byte offset of element (row, col) of a bfloat16 tile of ROWS rows staged in LDS as
+// 64-column blocks of ROWS x 128 bytes, the 16-byte chunks of each row
 // XOR-swizzled by (row / 2) % 8 so that the rows a write or read phase touches
 // spread over the banks.  Each block is laid out exactly like the matching
-// 32 KiB block of a k-blocked strip.
+// block of a k-blocked strip (32 KiB for 256 rows).
+template <int ROWS>
 __device__ __forceinline__ uint32_t tile_lds_byte(int row, int col) {
-  return (uint32_t)((col >> 6) * 32768 + row * 128 + ((((col & 63) >> 3) ^ ((row >> 1) & 7)) << 4) +
+  return (uint32_t)((col >> 6) * (ROWS * 128) + row * 128 + ((((col & 63) >> 3) ^ ((row >> 1) & 7)) << 4) +
                     (col & 7) * 2);
 }
 
-// Copies the 256 x 256 bfloat16 tile staged in LDS (see tile_lds_byte) to a
-// k-blocked strip: block b (columns 64 b .. 64 b + 63) goes to the 32 KiB at
+// Copies the ROWS x COLS bfloat16 tile staged in LDS (see tile_lds_byte) to a
+// k-blocked strip: block b (columns 64 b .. 64 b + 63) goes to the ROWS x 128 bytes at
 // element ((kb0 + b) * rows_pitch + r0) * 64, one 16-byte chunk per thread and
 // step, 1 KiB contiguous per wavefront store.
-template <int NT>
+template <int NT, int ROWS, int COLS>
 __device__ __forceinline__ void store_tile_blocked(const uint16_t* lds, uint16_t* __restrict__ dst,
                                                    uint32_t kb0, uint32_t rows_pitch, uint32_t r0) {
   const int tid = threadIdx.x;
 #pragma unroll
-  for (int q = 0; q < 8192 / NT; ++q) {
+  for (int q = 0; q < ROWS * COLS / 8 / NT; ++q) {
     const int c = q * NT + tid;  // 16-byte chunk of the tile
-    const int b = c >> 11, row = (c >> 3) & 255, ch = c & 7;
-    const uint4 v = *(const uint4*)((const char*)lds + b * 32768 + row * 128 + ((ch ^ ((row >> 1) & 7)) << 4));
+    const int b = c / (ROWS * 8), row = (c >> 3) % ROWS, ch = c & 7;
+    const uint4 v = *(const uint4*)((const char*)lds + b * (ROWS * 128) + row * 128 + ((ch ^ ((row >> 1) & 7)) << 4));
     *(uint4*)(dst + (((kb0 + (uint32_t)b) * rows_pitch + r0 + (uint32_t)row) * 64u + (uint32_t)ch * 8u)) = v;
   }
 }
@@ -960,7 +1123,7 @@ __device__ __forceinline__ void grad_tile(const GradArgs& a, int vt, int tb,
   S* __restrict__ Gt = (S*)a.strip_t;
   const uint32_t Tc = (uint32_t)a.Tc, Vc = (uint32_t)a.Vc;
   if constexpr (kBlocked) {
-    static_assert(BM == 256 && BN == 256, "the LDS staging holds one 256 x 256 tile");
+    static_assert(BM % 64 == 0 && BN % 64 == 0 && BM * BN % (8 * G::NT) == 0, "whole blocks and chunks");
     static_assert(G::LDS_ELEMS >= BM * BN, "the ring must hold one bfloat16 tile");
   }
   const bool full = m0 + BM <= a.M;  // no padding rows: no row mask
@@ -1059,17 +1222,17 @@ __device__ __forceinline__ void grad_tile(const GradArgs& a, int vt, int tb,
 #pragma unroll
         for (int r4 = 0; r4 < 16; r4 += 4) {
           const int tl = wn + 32 * j + (lane & 31), vl = wm + 32 * i + acc_row(r4, lane);
-          *(uint2*)((char*)lds + tile_lds_byte(tl, vl)) = packed[j][i][r4 >> 2];
+          *(uint2*)((char*)lds + tile_lds_byte<BN>(tl, vl)) = packed[j][i][r4 >> 2];
         }
     uint16_t tbits[NB];
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
       tbits[j] = (uint16_t)(E::pack2(vt_val[j], 0.f) & 0xFFFFu);
       if (trow[j] >= 0)
-        *(uint16_t*)((char*)lds + tile_lds_byte(wn + 32 * j + (lane & 31), trow[j])) = tbits[j];
+        *(uint16_t*)((char*)lds + tile_lds_byte<BN>(wn + 32 * j + (lane & 31), trow[j])) = tbits[j];
     }
     __syncthreads();
-    store_tile_blocked<G::NT>(lds, Gt, (uint32_t)m0 >> 6, Tc, (uint32_t)n0);
+    store_tile_blocked<G::NT, BN, BM>(lds, Gt, (uint32_t)m0 >> 6, Tc, (uint32_t)n0);
     __syncthreads();
     // G: the tile as rows of vocabulary ids, columns of tokens.
 #pragma unroll
@@ -1081,17 +1244,17 @@ __device__ __forceinline__ void grad_tile(const GradArgs& a, int vt, int tb,
           const int tl = wn + 32 * j + (lane & 31), vl = wm + 32 * i + acc_row(r4, lane);
           const uint2 p = packed[j][i][r4 >> 2];
           char* base = (char*)lds;
-          *(uint16_t*)(base + tile_lds_byte(vl, tl)) = (uint16_t)(p.x & 0xFFFFu);
-          *(uint16_t*)(base + tile_lds_byte(vl + 1, tl)) = (uint16_t)(p.x >> 16);
-          *(uint16_t*)(base + tile_lds_byte(vl + 2, tl)) = (uint16_t)(p.y & 0xFFFFu);
-          *(uint16_t*)(base + tile_lds_byte(vl + 3, tl)) = (uint16_t)(p.y >> 16);
+          *(uint16_t*)(base + tile_lds_byte<BM>(vl, tl)) = (uint16_t)(p.x & 0xFFFFu);
+          *(uint16_t*)(base + tile_lds_byte<BM>(vl + 1, tl)) = (uint16_t)(p.x >> 16);
+          *(uint16_t*)(base + tile_lds_byte<BM>(vl + 2, tl)) = (uint16_t)(p.y & 0xFFFFu);
+          *(uint16_t*)(base + tile_lds_byte<BM>(vl + 3, tl)) = (uint16_t)(p.y >> 16);
         }
 #pragma unroll
     for (int j = 0; j < NB; ++j)
       if (trow[j] >= 0)
-        *(uint16_t*)((char*)lds + tile_lds_byte(trow[j], wn + 32 * j + (lane & 31))) = tbits[j];
+        *(uint16_t*)((char*)lds + tile_lds_byte<BM>(trow[j], wn + 32 * j + (lane & 31))) = tbits[j];
     __syncthreads();
-    store_tile_blocked<G::NT>(lds, Gs, (uint32_t)n0 >> 6, Vc, (uint32_t)m0);
+    store_tile_blocked<G::NT, BM, BN>(lds, Gs, (uint32_t)n0 >> 6, Vc, (uint32_t)m0);
   }
 }
 
@@ -1101,6 +1264,21 @@ __device__ __forceinline__ void grad_tile(const GradArgs& a, int vt, int tb,
 template <class S>
 __global__ void __launch_bounds__(256) target_logit_kernel(TgtArgs a) {
   constexpr int VEC = 16 / (int)sizeof(S);
+  if (a.count && blockIdx.x == 0) {
+    __shared__ int bad[256];
+    int n = 0;
+    for (int64_t i = threadIdx.x; i < a.T; i += 256) {
+      const int64_t tg = a.targets[i];
+      n += tg != a.ignore_index && (tg < 0 || tg >= a.V);
+    }
+    bad[threadIdx.x] = n;
+    __syncthreads();
+    for (int o = 128; o > 0; o >>= 1) {
+      if ((int)threadIdx.x < o) bad[threadIdx.x] += bad[threadIdx.x + o];
+      __syncthreads();
+    }
+    if (threadIdx.x == 0) *a.count = (unsigned long long)bad[0];
+  }
   const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (t >= a.T) return;
@@ -1272,6 +1450,98 @@ __global__ void __launch_bounds__(GM::NT, GM::OCC)
   grad_tile<E, GL>(g, mt, nt, smem);
 }
 
+// One launch of the few-token backward: the dH and dW tiles of one strip and the
+// residual tiles of the next, as in bwd_stage_kernel, with three differences.  The
+// contractions read W and H as they are, transposed on the way out of LDS (a few per
+// cent of the mainloop's rate, where copies of W^T would cost 0.38 ms for V = 201088,
+// d = 2880 whatever T is); a strip holds several shards where they are small; and dH,
+// which has few tiles and long sums here, is split into jobs along the vocabulary.
+template <class E, class GL, class GC>
+__global__ void __launch_bounds__(GC::NT, GC::OCC* GC::NT / 256) few_stage_kernel(FewArgs a, StageSplit sp) {
+  static_assert(GL::NT == GC::NT && GL::BN == GC::BN && GL::BM == GC::BM, "one tile shape");
+  using S = typename E::storage;
+  constexpr int LDS = GL::LDS_ELEMS > GC::LDS_ELEMS ? GL::LDS_ELEMS : GC::LDS_ELEMS;
+  __shared__ __attribute__((aligned(16))) S smem[LDS];
+  const int xcd = blockIdx.x % 8;
+  int idx = blockIdx.x / 8, p = 0;
+  while (p < 2 && idx >= sp.cnt[p][xcd]) idx -= sp.cnt[p++][xcd];
+  idx += sp.first[p][xcd];
+  const int kind = a.order[p];
+  const int n_tb = (a.g.N + GL::BN - 1) / GL::BN, n_nb = (a.g.d + GC::BM - 1) / GC::BM;
+  const int64_t d = a.g.d, Tc = a.g.Tc;
+  if (kind == 2) {  // token blocks of one row tile side by side: they share its W
+    const int row = idx / n_tb * GL::BM;
+    int q = 0;
+    while (q + 1 < a.n_gseg && row >= a.gseg[q + 1].row0) ++q;
+    GradArgs g = a.g;
+    g.W = a.gseg[q].w;
+    g.gid0 = a.gseg[q].gid0;
+    g.M = a.gseg[q].rows;
+    const int64_t row0 = a.gseg[q].row0;
+    g.strip = (S*)g.strip + row0 * E::KB;
+    g.strip_t = (S*)g.strip_t + row0 / E::KB * Tc * E::KB;
+    grad_tile<E, GL>(g, (row - (int)row0) / GL::BM, idx % n_tb, smem);
+    return;
+  }
+  GemmArgs h;
+  int mt, nt;
+  h.ldb = h.ldc = d;
+  h.lda = E::KB;
+  h.N = (int32_t)d;
+  h.kblkb = 0;
+  if (kind == 0) {
+    const int per = n_tb * n_nb;
+    const FewJob job = a.job[idx / per];
+    mt = idx % per % n_tb;
+    nt = idx % per / n_tb;
+    const FewSeg& sg = a.cseg[job.seg];
+    h.B = (const S*)sg.w + (int64_t)job.k0 * d;
+    h.A = (const S*)a.Gt + (int64_t)(sg.row0 + job.k0) / E::KB * Tc * E::KB;
+    h.kblka = Tc * E::KB;
+    h.C = a.part + (int64_t)(idx / per) * a.g.N * d;
+    h.M = a.g.N;
+    h.K = job.rows;
+    h.beta = job.beta;
+  } else {
+    const int row = idx / n_nb * GC::BN;
+    nt = idx % n_nb;
+    int q = 0;
+    while (q + 1 < a.n_cseg && row >= a.cseg[q + 1].row0) ++q;
+    const FewSeg& sg = a.cseg[q];
+    mt = (row - sg.row0) / GC::BN;
+    if (mt * GC::BN >= sg.rows) return;  // padding of the segment
+    h.B = a.g.H;
+    h.A = (const S*)a.G + (int64_t)sg.row0 * E::KB;
+    h.kblka = a.g.Vc * E::KB;
+    h.C = sg.dw;
+    h.M = sg.rows;
+    h.K = a.g.N;
+    h.beta = a.beta_w;
+  }
+  const int n0 = nt * GC::BM;
+  if (n0 + GC::BM > (int)d)
+    gemm_tile<E, GC, true>(h, mt, n0, smem);
+  else
+    gemm_tile<E, GC>(h, mt, n0, smem);
+}
+
+__global__ void __launch_bounds__(256) sum_parts_kernel(const float4* __restrict__ part, int n,
+                                                        int64_t len, float4* __restrict__ out) {
+  const int64_t stride = (int64_t)gridDim.x * 256;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < len; i += stride) {
+    float4 s = part[i];
+#pragma unroll 4
+    for (int k = 1; k < n; ++k) {
+      const float4 v = part[(int64_t)k * len + i];
+      s.x += v.x;
+      s.y += v.y;
+      s.z += v.z;
+      s.w += v.w;
+    }
+    out[i] = s;
+  }
+}
+
 // out = in^T in the k-blocked layout: in is row-major [R][ld_in]; out is
 // [R_pad / KB][C][KB] with KB = 128 / sizeof(S) (element (c, r) at
 // ((r / KB) C + c) KB + r % KB), zero for R <= r < R_pad.  One 64 x 64 tile per
@@ -1341,6 +1611,9 @@ template <> struct Cfg<Bf16> {
   using LogitsTail = GemmDma<256, 256, 2, 4, 64, 2, Bf16, true>;
   using Stream128 = Ring<256, 128, 4, 2, 3, Bf16>;  // forward on few tokens, see fwd_tile
   using Stream64 = Ring<128, 64, 4, 2, 6, Bf16>;
+  using FewC = GemmDma<256, 256, 2, 4, 64, 2, Bf16, false, true>;  // few-token backward
+  using FewLs = Ring<128, 64, 4, 2, 3, Bf16>;
+  using FewCs = Ring<128, 64, 4, 2, 3, Bf16, true>;
   static constexpr int KALIGN = 64;  // K granularity the dH / dW launches need
 };
 template <> struct Cfg<F32> {
@@ -1352,6 +1625,9 @@ template <> struct Cfg<F32> {
   using LogitsTail = GemmDma<256, 256, 2, 4, 64, 2, F32, true>;
   using Stream128 = Ring<256, 128, 4, 2, 3, F32>;
   using Stream64 = Ring<128, 64, 4, 2, 6, F32>;
+  using FewC = GemmDma<256, 256, 2, 4, 64, 2, F32, false, true>;
+  using FewLs = Ring<128, 64, 4, 2, 3, F32>;
+  using FewCs = Ring<128, 64, 4, 2, 3, F32, true>;
   static constexpr int KALIGN = 32;  // K granularity the dH / dW launches need
 };
 
@@ -1437,6 +1713,25 @@ static bool launch_stage(const GemmArgs& h, const GemmArgs& w, const GradArgs& g
   return launch_stage_g<E, typename Cfg<E>::LogitsTail, Mm, Wd>(h, w, g, s);
 }
 
+template <class E, class GL, class GC>
+static bool launch_few_g(const FewArgs& a, hipStream_t s) {
+  const int n_tb = (a.g.N + GL::BN - 1) / GL::BN, n_nb = (a.g.d + GC::BM - 1) / GC::BM;
+  const int tiles[3] = {a.n_job * n_tb * n_nb, a.w_tiles * n_nb, a.g_tiles * n_tb};
+  int n_kind[3], n = 0;
+  for (int p = 0; p < 3; ++p) n += n_kind[p] = tiles[a.order[p]];
+  if (n == 0) return true;
+  hipLaunchKernelGGL((few_stage_kernel<E, GL, GC>), dim3((unsigned)n), dim3(GC::NT), 0, s, a,
+                     split_stage(n_kind));
+  return launched_ok();
+}
+template <class E>
+static bool launch_few(int cls, const FewArgs& a, hipStream_t s) {
+  using C = Cfg<E>;
+  if (cls == 1) return launch_few_g<E, typename C::FewLs, typename C::FewCs>(a, s);
+  if (a.g.d % E::KB == 0) return launch_few_g<E, typename C::Logits, typename C::FewC>(a, s);
+  return launch_few_g<E, typename C::LogitsTail, typename C::FewC>(a, s);
+}
+
 // ---------------------------------------------------------------------------
 // Library-owned forward workspace for callers that cannot allocate (see
 // vp_ce_forward_noalloc).  Each device the library runs on holds its own copy
@@ -1507,6 +1802,26 @@ static FwdTile fwd_tile_of(int kind) {
 }
 FwdTile fwd_tile(int dtype, int kind) {
   return dtype == 1 ? fwd_tile_of<Bf16>(kind) : fwd_tile_of<F32>(kind);
+}
+
+template <class E>
+static FewTile few_tile_of(int cls) {
+  constexpr bool b16 = sizeof(typename E::storage) == 2;
+  using G0 = typename Cfg<E>::FewC;
+  using G1 = typename Cfg<E>::FewCs;
+  return cls ? FewTile{G1::BM, G1::BN, b16 ? 0.47 : 1.33} : FewTile{G0::BM, G0::BN, b16 ? 1.4 : 7.45};
+}
+FewTile few_tile(int dtype, int cls) {
+  return dtype == 1 ? few_tile_of<Bf16>(cls) : few_tile_of<F32>(cls);
+}
+bool run_few_stage(int dtype, int cls, const FewArgs& a, hipStream_t s) {
+  return dtype == 1 ? launch_few<Bf16>(cls, a, s) : launch_few<F32>(cls, a, s);
+}
+bool run_sum_parts(const float* part, int n, int64_t len, float* out, hipStream_t s) {
+  const int64_t vecs = len / 4, blocks = std::min<int64_t>((vecs + 255) / 256, 2048);
+  hipLaunchKernelGGL(sum_parts_kernel, dim3((unsigned)blocks), dim3(256), 0, s, (const float4*)part, n,
+                     vecs, (float4*)out);
+  return launched_ok();
 }
 
 bool run_ws_init(unsigned long long* counter, hipStream_t s) {
