@@ -147,18 +147,19 @@ FwdPlan plan_fwd(const vp_problem* p, int64_t slots) {
   return best;
 }
 
-// Backward plan.  The softmax residual of a strip of Tc tokens by Vc
+// The backward's workspace.  The softmax residual of a strip of Tc tokens by Vc
 // vocabulary rows is staged in both layouts (G [Vc][Tc] and G^T [Tc][Vc]),
 // twice: one launch writes the residual of strip c+1 while it contracts strip
 // c into dH and dW.  Tc*Vc <= budget; tokens in balanced chunks no larger than
 // the square root of the budget (the float32 read-modify-write traffic of dH
 // across vocabulary chunks plus that of dW across token chunks is proportional
 // to 1/Vc + 1/Tc).  The workspace also holds H^T [d][T_pad] (written once per
-// call) and W^T [d][Vc] of the current vocabulary chunk.  Nothing here depends
-// on V.
+// call) and W^T [d][Vc] of the current vocabulary chunk; a backward that reads W and H
+// as they are uses that room for longer strips and partial sums of dH (plan_bwd).
+// Nothing here depends on V.
 struct StripPlan {
   int64_t Tc, Vc, T_pad;
-  size_t off_g[2], off_gt[2], off_ht, off_wt, off_yt, total;
+  size_t total;
 };
 
 StripPlan strip_plan(const vp_problem* p) {
@@ -172,17 +173,8 @@ StripPlan strip_plan(const vp_problem* p) {
                                                         32768));
   s.T_pad = round_up(T, 256);
   const size_t eb = elem_bytes(p->dtype);
-  const size_t strip = align256((size_t)s.Vc * s.Tc * eb);
-  size_t off = kHeaderBytes;
-  for (int b = 0; b < 2; ++b) {
-    s.off_g[b] = off;
-    s.off_gt[b] = off + strip;
-    off += 2 * strip;
-  }
-  s.off_ht = off;
-  s.off_wt = s.off_ht + align256((size_t)p->d * s.T_pad * eb);
-  s.off_yt = s.off_wt + align256((size_t)p->d * s.Vc * eb);
-  s.total = s.off_yt + align256((size_t)T * 4);
+  s.total = kHeaderBytes + 4 * align256((size_t)s.Vc * s.Tc * eb) + align256((size_t)p->d * s.T_pad * eb) +
+            align256((size_t)p->d * s.Vc * eb) + align256((size_t)T * 4);
   return s;
 }
 
@@ -224,258 +216,232 @@ vp_status check_shards(const vp_problem* p, const void* const* W_shards) {
   return VP_OK;
 }
 
-// The strips of a backward call in visiting order: shards in `order`, each cut
-// into balanced, tile-aligned vocabulary chunks (never above Vc), each chunk
-// meeting every token chunk.
-struct Chunk {
-  int q;
-  int64_t v0, M, t0, N;
-  bool new_vchunk, first_vchunk;
-};
-
-std::vector<Chunk> strip_chunks(const vp_problem* prob, const StripPlan& plan) {
-  const vpce::TileShape ts = vpce::tile_shape(prob->dtype);
-  std::vector<Chunk> chunks;
-  bool first = true;
-  for (int i = 0; i < prob->P; ++i) {
-    const int q = prob->order ? prob->order[i] : i;
-    const int64_t Vq = prob->shard_rows[q];
-    if (Vq == 0) continue;
-    const int64_t vc =
-        std::min<int64_t>(plan.Vc, round_up(ceil_div(Vq, ceil_div(Vq, plan.Vc)), ts.grad_bm));
-    for (int64_t v0 = 0; v0 < Vq; v0 += vc) {
-      for (int64_t t0 = 0; t0 < prob->T; t0 += plan.Tc)
-        chunks.push_back({q, v0, std::min<int64_t>(vc, Vq - v0), t0,
-                          std::min<int64_t>(plan.Tc, prob->T - t0), t0 == 0, first});
-      first = false;
-    }
-  }
-  return chunks;
-}
-
-// The backward on few tokens (one token chunk of at most kFewBwdTokens): strips of one
-// or several shards, dH split into jobs along the vocabulary (see few_stage_kernel).
-// Everything is laid out in the workspace that strip_plan asks for; without H^T and
-// W^T in it there is room for partial dH sums and for longer strips.
-constexpr int64_t kFewBwdTokens = 2048;
-struct FewStrip {
+// How a backward is cut: tile class, token chunks of Tc, vocabulary strips of at most Vc
+// padded rows, dH partial sums.  Everything is laid out in the workspace that strip_plan
+// asks for.
+struct BwdStrip {  // vocabulary side of the strips; each meets every token chunk
   struct Seg {
     int q;
     int64_t v0, rows, row0;
   };
   std::vector<Seg> segs;
-  std::vector<vpce::FewJob> jobs;
+  std::vector<vpce::StageJob> jobs;
   int64_t rows_pad = 0;
 };
-struct FewPlan {
-  int cls = -1;
-  int64_t Tc = 0, Vr = 0;
+struct BwdPlan {
+  int cls = 0, slots = 1;
+  int64_t Tc = 0, Vc = 0;  // Vc: most padded rows a strip may have
+  double time = -1;
+  // filled in by cut_strips
+  std::vector<BwdStrip> strips;
+  int64_t Vr = 0;  // padded rows of the longest strip
   int max_jobs = 1;
-  size_t off_g[2], off_gt[2], off_part, off_yt;
-  double time = 0;
-  std::vector<FewStrip> strips;
+  size_t off_g[2], off_gt[2], off_part, off_ht, off_wt, off_yt;
 };
 
-// Plan for one tile class; false if the workspace has no room for it.
-bool few_plan_cls(const vp_problem* p, size_t total, int cls, FewPlan* out) {
-  const vpce::FewTile ft = vpce::few_tile(p->dtype, cls);
-  const int64_t eb = (int64_t)elem_bytes(p->dtype), KB = vpce::tile_shape(p->dtype).kblock;
-  const int64_t T = p->T, d = p->d, slot = T * d * 4;
-  const int64_t budget = p->strip_elems > 0 ? p->strip_elems : kDefaultStrip;
-  FewPlan f;
-  f.cls = cls;
-  f.Tc = round_up(T, ft.bn);
-  const int64_t avail = (int64_t)total - (int64_t)kHeaderBytes - (int64_t)align256((size_t)T * 4) - 5 * 256;
-  // at most a quarter of the workspace for partial sums, the rest for the strips
-  const int64_t slots = std::max<int64_t>(1, std::min<int64_t>(avail / 4 / slot, vpce::kMaxJobs));
-  const int64_t room = avail - (slots > 1 ? slots * slot : 0);
-  const int64_t cap = round_down(std::min(budget / f.Tc, room / (4 * f.Tc * eb)), ft.bm);
-  if (cap < ft.bm) return false;
-
-  // Strips: a shard above the cap is cut into balanced pieces, a strip each; smaller
-  // shards share a strip while they fit.  A shard of less than 256 rows keeps a strip
-  // of its own (beside others it would be padding for the most part).
+// Walks the strips of a plan's vocabulary side in visiting order: a shard above Vc is cut
+// into balanced pieces, a strip each; smaller shards share a strip while they fit.  A
+// shard of less than 256 rows keeps a strip of its own (beside others it would be padding
+// for the most part).  seg(new_strip, q, v0, rows, padded rows) for every segment.
+template <class F>
+void walk_strips(const vp_problem* p, int64_t Vc, int bm, F&& seg) {
+  int64_t used = 0, last_rows = 0;
+  int n_seg = 0;
   for (int i = 0; i < p->P; ++i) {
     const int q = p->order ? p->order[i] : i;
-    const int64_t Vq = p->shard_rows[q];
+    const int64_t Vq = p->shard_rows[q], pad = round_up(Vq, bm);
     if (Vq == 0) continue;
-    const int64_t pad = round_up(Vq, ft.bm);
-    if (pad <= cap) {
-      const bool join = !f.strips.empty() && f.strips.back().rows_pad + pad <= cap && Vq >= 256 &&
-                        f.strips.back().segs.back().rows >= 256 &&
-                        f.strips.back().segs.back().rows == p->shard_rows[f.strips.back().segs.back().q] &&
-                        (int64_t)f.strips.back().segs.size() < std::min<int64_t>(slots, vpce::kMaxSegs);
-      if (!join) f.strips.emplace_back();
-      f.strips.back().segs.push_back({q, 0, Vq, f.strips.back().rows_pad});
-      f.strips.back().rows_pad += pad;
+    if (pad <= Vc) {
+      const bool join = n_seg > 0 && n_seg < vpce::kMaxSegs && used + pad <= Vc && Vq >= 256 && last_rows >= 256;
+      seg(!join, q, (int64_t)0, Vq, pad);
+      n_seg = join ? n_seg + 1 : 1;
+      used = join ? used + pad : pad;
+      last_rows = Vq;
       continue;
     }
-    const int64_t vc = round_up(ceil_div(Vq, ceil_div(Vq, cap)), ft.bm);
+    const int64_t vc = round_up(ceil_div(Vq, ceil_div(Vq, Vc)), bm);
     for (int64_t v0 = 0; v0 < Vq; v0 += vc) {
       const int64_t rows = std::min(vc, Vq - v0);
-      f.strips.emplace_back();
-      f.strips.back().segs.push_back({q, v0, rows, 0});
-      f.strips.back().rows_pad = round_up(rows, ft.bm);
+      seg(true, q, v0, rows, round_up(rows, bm));
     }
+    n_seg = 0;  // nothing joins a piece
   }
-  for (const FewStrip& st : f.strips) f.Vr = std::max(f.Vr, st.rows_pad);
+}
 
-  // Jobs: a dH tile's sum should take no longer than half of what its launch gives a CU
-  // to do, counted in slices of all its tiles (and no less than eight slices).
-  const int64_t n_tb = ceil_div(T, ft.bn), n_nb = ceil_div(d, ft.bm);
-  const int64_t n = (int64_t)f.strips.size();
-  auto res_slices = [&](const FewStrip& st) { return st.rows_pad / ft.bm * n_tb * ceil_div(d, KB); };
-  std::vector<bool> used(vpce::kMaxJobs, false);
-  f.time = ft.us * ((double)res_slices(f.strips[0]) / kCUs + 0.5 * ceil_div(d, KB));
-  for (int64_t k = 0; k < n; ++k) {
-    FewStrip& st = f.strips[k];
-    int64_t ks = 0;
-    for (const FewStrip::Seg& sg : st.segs) ks += ceil_div(sg.rows, KB);
-    const int64_t work = n_tb * n_nb * ks + ceil_div(st.rows_pad, ft.bn) * n_nb * ceil_div(T, KB) +
-                         (k + 1 < n ? res_slices(f.strips[k + 1]) : 0);
-    int64_t target = std::max<int64_t>(8, work / kCUs / 2);
-    for (;; target += target / 4) {
-      int64_t jobs = 0;
-      for (const FewStrip::Seg& sg : st.segs) jobs += ceil_div(ceil_div(sg.rows, KB), target);
-      if (jobs <= std::max<int64_t>(slots, (int64_t)st.segs.size())) break;
+// Slices that a strip's dH sum has, and the most that one job should take: half of what
+// its launch gives a CU to do, no less than eight, and as many as the slots ask for.
+int64_t job_slices(int64_t ks, int64_t launch_work, int slots) {
+  return std::max(std::max<int64_t>(8, launch_work / kCUs / 2), ceil_div(ks, slots));
+}
+
+// Estimated time (us) of a plan's launches.  A launch takes its slices (with two more per
+// tile for its ends) spread over the CUs and half of its longest tile for the last round,
+// or that tile alone; about 8 us of launch and fill; and 0.3 of the time its bytes take at
+// 5 TB/s, the part that does not hide behind the rest.  Fitted to backwards of T = 40 to
+// 2048 tokens, d = 256 to 4096, V = 2048 to 201088: classes 0 to 2 within 10 to 15%, and
+// the class it picks within 1% of the fastest one on average (10% at worst).
+double plan_time(const vp_problem* p, const BwdPlan& f) {
+  constexpr int64_t kEnds = 2;
+  const vpce::BwdTile ft = vpce::bwd_tile(p->dtype, f.cls);
+  const int64_t KB = vpce::tile_shape(p->dtype).kblock, kd = ceil_div(p->d, KB), d = p->d;
+  const int64_t eb = (int64_t)elem_bytes(p->dtype), n_nb = vpce::bwd_col_blocks(f.cls, (int)d);
+  const int64_t n_tc = ceil_div(p->T, f.Tc), N = std::min(f.Tc, p->T);
+  const int64_t n_tb = ceil_div(N, ft.bn), kt = ceil_div(N, KB);
+  auto launch = [&](int64_t work, int64_t longest, int64_t bytes) {
+    const double mm = std::max((double)work / kCUs + 0.5 * longest, (double)longest);
+    return ft.us * mm + 0.3 * (double)bytes / 5e6 + 8.0;
+  };
+  double total = 0;
+  int64_t slices = 0, pads = 0;         // of the strip being walked
+  int64_t c_work = 0, c_long = 0, c_bytes = 0;  // contractions left to the next launch
+  auto close = [&]() {
+    if (pads == 0) return;
+    const int64_t res = pads / ft.bm * n_tb * (kd + kEnds);
+    const int64_t dw = ceil_div(pads, ft.bn) * n_nb * (kt + kEnds);
+    const int64_t per = std::min(slices, job_slices(slices, res + dw + n_tb * n_nb * slices, f.slots));
+    const int64_t jobs = ceil_div(slices, per), dh = n_tb * n_nb * (slices + jobs * kEnds);
+    const int64_t strip = 2 * pads * N * eb;
+    total += launch(res + c_work, std::max(kd + kEnds, c_long), pads * d * eb + strip + c_bytes);
+    c_work = dw + dh;
+    c_long = std::max(per, kt) + kEnds;
+    c_bytes = pads * d * (eb + 4) + strip + 2 * jobs * N * d * 4;
+    total += (double)(n_tc - 1) * launch(res + c_work, std::max(kd + kEnds, c_long), pads * d * eb + strip + c_bytes);
+    if (jobs > 1) total += (double)(jobs * p->T * d * 4) / 5e6;
+  };
+  walk_strips(p, f.Vc, ft.bm, [&](bool fresh, int, int64_t, int64_t rows, int64_t pad) {
+    if (fresh) {
+      close();
+      slices = pads = 0;
     }
-    int64_t longest = std::max(ceil_div(d, KB), ceil_div(T, KB));
-    for (size_t i = 0; i < st.segs.size(); ++i) {
-      const int64_t blocks = ceil_div(st.segs[i].rows, KB);
-      const int64_t per = ceil_div(blocks, ceil_div(blocks, target));
-      for (int64_t b = 0; b < blocks; b += per) {
-        const size_t j = st.jobs.size();
-        st.jobs.push_back({(int32_t)i, (int32_t)(b * KB),
-                           (int32_t)(std::min(st.segs[i].rows, (b + per) * KB) - b * KB), used[j] ? 1 : 0});
-        used[j] = true;
+    slices += ceil_div(rows, KB);
+    pads += pad;
+  });
+  close();
+  total += launch(c_work, c_long, c_bytes);
+  if (f.cls == 3) {  // the transposed copies, at 5 TB/s
+    int64_t V = 0;
+    for (int q = 0; q < p->P; ++q) V += p->shard_rows[q];
+    total += 2.0 * (double)(V + p->T) * d * eb / 5e6;
+  }
+  return total;
+}
+
+// The plan with the shortest estimated time, of the tile classes, one or many dH partial
+// sums, and two ways to cut the tokens: the strip plan's balanced chunks of at most the
+// root of the budget, or longer ones where the whole vocabulary is shorter than that.
+BwdPlan plan_bwd(const vp_problem* p) {
+  const StripPlan s = strip_plan(p);
+  const int64_t eb = (int64_t)elem_bytes(p->dtype);
+  const int64_t budget = p->strip_elems > 0 ? p->strip_elems : kDefaultStrip;
+  const int64_t avail = (int64_t)s.total - (int64_t)kHeaderBytes - (int64_t)align256((size_t)p->T * 4) - 5 * 256;
+  const int64_t slot = p->T * p->d * 4;
+  BwdPlan best;
+  auto consider = [&](int cls, int slots, int64_t Tc, int64_t Vc) {
+    BwdPlan f;
+    f.cls = cls;
+    f.slots = slots;
+    f.Tc = Tc;
+    f.Vc = Vc;
+    f.time = plan_time(p, f);
+    if (best.time < 0 || f.time < best.time) best = std::move(f);
+  };
+  consider(3, 1, s.Tc, s.Vc);
+  for (int cls = p->dtype == VP_BF16 ? 0 : 1; cls < 3; ++cls) {
+    const vpce::BwdTile ft = vpce::bwd_tile(p->dtype, cls);
+    int64_t rows = 0;
+    for (int q = 0; q < p->P; ++q) rows += round_up(p->shard_rows[q], ft.bm);
+    int64_t tcs[2] = {std::min(s.Tc, round_up(p->T, ft.bn)), 0};
+    const int64_t most = round_down(std::min(budget / rows, avail / (4 * eb * rows)), ft.bn);
+    if (most > tcs[0] && tcs[0] < p->T)
+      tcs[1] = std::min(most, round_up(ceil_div(p->T, ceil_div(p->T, most)), ft.bn));
+    for (int64_t Tc : tcs) {
+      if (Tc <= 0) continue;
+      for (int slots = 1; slots <= vpce::kMaxJobs; slots *= 2) {
+        const int64_t room = avail - (slots > 1 ? slots * slot : 0);
+        int64_t Vc = round_down(std::min(budget / Tc, room / (4 * Tc * eb)), ft.bm);
+        if (Vc < ft.bm && slots == 1) Vc = ft.bm;  // strip_plan has room for it
+        if (room <= 0 || Vc < ft.bm) break;
+        consider(cls, slots, Tc, Vc);
       }
-      longest = std::max(longest, per);
     }
-    f.max_jobs = std::max(f.max_jobs, (int)st.jobs.size());
-    f.time += ft.us * ((double)work / kCUs + 0.5 * longest);
   }
+  return best;
+}
 
-  const size_t strip = align256((size_t)(f.Vr * f.Tc * eb));
+// The strips, dH jobs and workspace layout of a plan.
+void cut_strips(const vp_problem* p, BwdPlan* f) {
+  const vpce::BwdTile ft = vpce::bwd_tile(p->dtype, f->cls);
+  const int64_t KB = vpce::tile_shape(p->dtype).kblock, eb = (int64_t)elem_bytes(p->dtype);
+  walk_strips(p, f->Vc, ft.bm, [&](bool fresh, int q, int64_t v0, int64_t rows, int64_t pad) {
+    if (fresh) f->strips.emplace_back();
+    BwdStrip& st = f->strips.back();
+    st.segs.push_back({q, v0, rows, st.rows_pad});
+    st.rows_pad += pad;
+  });
+  const int64_t N = std::min(f->Tc, p->T), n_tb = ceil_div(N, ft.bn);
+  const int64_t n_nb = vpce::bwd_col_blocks(f->cls, (int)p->d);
+  bool used[vpce::kMaxJobs] = {false};
+  for (BwdStrip& st : f->strips) {
+    f->Vr = std::max(f->Vr, st.rows_pad);
+    int64_t ks = 0;
+    for (const BwdStrip::Seg& sg : st.segs) ks += ceil_div(sg.rows, KB);
+    const int64_t work = st.rows_pad / ft.bm * n_tb * ceil_div(p->d, KB) +
+                         ceil_div(st.rows_pad, ft.bn) * n_nb * ceil_div(N, KB) + n_tb * n_nb * ks;
+    int64_t per = job_slices(ks, work, f->slots);
+    auto add = [&](int seg, int n_seg, int64_t k0, int64_t rows) {
+      const size_t j = st.jobs.size();
+      st.jobs.push_back({seg, n_seg, (int32_t)k0, (int32_t)rows, used[j] ? 1 : 0});
+      used[j] = true;
+    };
+    // whole segments gather in a job up to `per` slices; a longer segment is cut
+    for (;; per += ceil_div(per, 4)) {
+      int n = 0;
+      int64_t have = 0;
+      for (const BwdStrip::Seg& sg : st.segs) {
+        const int64_t b = ceil_div(sg.rows, KB);
+        if (have > 0 && have + b <= per) {
+          have += b;
+          continue;
+        }
+        n += (int)ceil_div(b, per);
+        have = b <= per ? b : per;  // nothing gathers behind a cut segment
+      }
+      if (n <= f->slots || f->slots == 1) break;
+    }
+    if (f->slots == 1) {
+      add(0, (int)st.segs.size(), 0, st.segs.size() == 1 ? st.segs[0].rows : 0);
+    } else {
+      int64_t have = 0;
+      for (size_t i = 0; i < st.segs.size(); ++i) {
+        const int64_t b = ceil_div(st.segs[i].rows, KB);
+        if (have > 0 && have + b <= per) {
+          ++st.jobs.back().n_seg;
+          have += b;
+          continue;
+        }
+        const int64_t step = ceil_div(b, ceil_div(b, per));
+        for (int64_t k = 0; k < b; k += step)
+          add((int)i, 1, k * KB, std::min(st.segs[i].rows, (k + step) * KB) - k * KB);
+        have = b <= per ? b : per;
+      }
+    }
+    f->max_jobs = std::max(f->max_jobs, (int)st.jobs.size());
+  }
+  const size_t strip = align256((size_t)(f->Vr * f->Tc * eb));
   size_t off = kHeaderBytes;
   for (int b = 0; b < 2; ++b) {
-    f.off_g[b] = off;
-    f.off_gt[b] = off + strip;
+    f->off_g[b] = off;
+    f->off_gt[b] = off + strip;
     off += 2 * strip;
   }
-  f.off_part = off;
-  if (f.max_jobs > 1) off += align256((size_t)(f.max_jobs * slot));
-  f.off_yt = off;
-  if (off + align256((size_t)T * 4) > total) return false;
-  *out = std::move(f);
-  return true;
-}
-
-// The plan of the class with the shorter estimated time; false for problems that run
-// the general backward (more tokens than kFewBwdTokens, several token chunks, or a
-// strip budget too small for one tile).
-bool few_plan(const vp_problem* p, FewPlan* out) {
-  if (p->T == 0 || p->T > kFewBwdTokens) return false;
-  const StripPlan s = strip_plan(p);
-  if (s.Tc < p->T) return false;
-  bool found = false;
-  for (int cls = 0; cls < 2; ++cls) {
-    FewPlan f;
-    if (few_plan_cls(p, s.total, cls, &f) && (!found || f.time < out->time)) {
-      *out = std::move(f);
-      found = true;
-    }
+  f->off_part = off;
+  if (f->max_jobs > 1) off += align256((size_t)(f->max_jobs * p->T * p->d * 4));
+  f->off_ht = f->off_wt = off;
+  if (f->cls == 3) {
+    f->off_wt = f->off_ht + align256((size_t)(p->d * round_up(p->T, 256) * eb));
+    off = f->off_wt + align256((size_t)(p->d * f->Vr * eb));
   }
-  return found;
-}
-
-vp_status backward_few(const vp_problem* p, const FewPlan& f, int64_t V, const void* H,
-                       const void* const* W_shards, const int64_t* targets, const float* lse,
-                       const float* grad_loss, float* dH, float* const* dW_shards, void* ws,
-                       hipStream_t s) {
-  const int64_t T = p->T, d = p->d;
-  const size_t eb = elem_bytes(p->dtype);
-  const vpce::FewTile ft = vpce::few_tile(p->dtype, f.cls);
-  char* wsb = (char*)ws;
-  float* yt = (float*)(wsb + f.off_yt);
-  float* part = f.max_jobs > 1 ? (float*)(wsb + f.off_part) : dH;
-
-  vpce::TgtArgs ta;
-  memset(&ta, 0, sizeof(ta));
-  int32_t n_tiles = 0;
-  build_table(p, W_shards, ft.bm, &ta.st, &n_tiles);
-  ta.H = H;
-  ta.targets = targets;
-  ta.T = T;
-  ta.V = V;
-  ta.d = (int32_t)d;
-  ta.yt = yt;
-  ta.count = (unsigned long long*)ws;
-  ta.ignore_index = p->ignore_index;
-  if (!vpce::run_target_logits(p->dtype, ta, s)) return VP_ERR_HIP;
-
-  int64_t off[VP_MAX_SHARDS];
-  int64_t acc = 0;
-  for (int q = 0; q < p->P; ++q) {
-    off[q] = acc;
-    acc += p->shard_rows[q];
-  }
-  auto segments = [&](const FewStrip& st, vpce::FewSeg* out) {
-    for (size_t i = 0; i < st.segs.size(); ++i) {
-      const FewStrip::Seg& sg = st.segs[i];
-      out[i].w = (const char*)W_shards[sg.q] + (size_t)(sg.v0 * d) * eb;
-      out[i].dw = dW_shards[sg.q] + sg.v0 * d;
-      out[i].gid0 = off[sg.q] + sg.v0;
-      out[i].rows = (int32_t)sg.rows;
-      out[i].row0 = (int32_t)sg.row0;
-    }
-    return (int32_t)st.segs.size();
-  };
-  // Launch k writes the residual of strip k (into buffer k % 2) and contracts strip
-  // k - 1 (from the other one), as the general backward does.
-  const int64_t n = (int64_t)f.strips.size(), KB = vpce::tile_shape(p->dtype).kblock;
-  for (int64_t k = 0; k <= n; ++k) {
-    vpce::FewArgs a;
-    memset(&a, 0, sizeof(a));
-    a.g.H = H;
-    a.g.targets = targets;
-    a.g.lse = lse;
-    a.g.grad = grad_loss;
-    a.g.strip = wsb + f.off_g[k % 2];
-    a.g.strip_t = wsb + f.off_gt[k % 2];
-    a.g.Tc = f.Tc;
-    a.g.Vc = f.Vr;
-    a.g.V = V;
-    a.g.ignore_index = p->ignore_index;
-    a.g.yt = yt;
-    a.g.N = (int32_t)T;
-    a.g.d = (int32_t)d;
-    if (k < n) {
-      a.n_gseg = segments(f.strips[k], a.gseg);
-      a.g_tiles = (int32_t)(f.strips[k].rows_pad / ft.bm);
-    }
-    int64_t longest = 0;
-    if (k >= 1) {
-      const FewStrip& st = f.strips[k - 1];
-      a.n_cseg = segments(st, a.cseg);
-      a.n_job = (int32_t)st.jobs.size();
-      for (size_t j = 0; j < st.jobs.size(); ++j) {
-        a.job[j] = st.jobs[j];
-        longest = std::max<int64_t>(longest, ceil_div(st.jobs[j].rows, KB));
-      }
-      a.w_tiles = (int32_t)ceil_div(st.rows_pad, ft.bn);
-      a.G = wsb + f.off_g[(k - 1) % 2];
-      a.Gt = wsb + f.off_gt[(k - 1) % 2];
-      a.part = part;
-      a.beta_w = (p->flags & VP_ACCUMULATE_DW) != 0;
-    }
-    // the kinds with the longest sums first, so that the last round of tiles is short
-    const int64_t slices[3] = {longest, ceil_div(T, KB), ceil_div(d, KB)};
-    for (int i = 0; i < 3; ++i) a.order[i] = i;
-    std::sort(a.order, a.order + 3, [&](int x, int y) { return slices[x] > slices[y]; });
-    if (!vpce::run_few_stage(p->dtype, f.cls, a, s)) return VP_ERR_HIP;
-  }
-  if (f.max_jobs > 1 && !vpce::run_sum_parts(part, f.max_jobs, T * d, dH, s)) return VP_ERR_HIP;
-  return VP_OK;
+  f->off_yt = off;
 }
 
 }  // namespace
@@ -703,20 +669,17 @@ vp_status vp_ce_plan_info(const vp_problem* prob, vp_plan_info* info) {
   const vp_status st = validate(prob, nullptr);
   if (st != VP_OK) return st;
   if (!info) return VP_ERR_NULL;
-  FewPlan few;
-  if (few_plan(prob, &few)) {
-    info->Tc = few.Tc;
-    info->Vc = few.Vr;
-    info->strips = (int64_t)few.strips.size();
-    info->stage_launches = info->strips + 1;
-    return VP_OK;
-  }
-  const StripPlan plan = strip_plan(prob);
-  const int64_t n = prob->T > 0 ? (int64_t)strip_chunks(prob, plan).size() : 0;
+  vp_problem p = *prob;
+  p.T = std::max<int64_t>(p.T, 1);
+  const BwdPlan plan = plan_bwd(&p);
+  int64_t n = 0;
+  walk_strips(&p, plan.Vc, vpce::bwd_tile(p.dtype, plan.cls).bm,
+              [&](bool fresh, int, int64_t, int64_t, int64_t) { n += fresh; });
+  if (prob->T == 0) n = 0;
   info->Tc = plan.Tc;
   info->Vc = plan.Vc;
-  info->strips = n;
-  info->stage_launches = n > 0 ? n + 1 : 0;
+  info->strips = n * ceil_div(p.T, plan.Tc);
+  info->stage_launches = info->strips > 0 ? info->strips + 1 : 0;
   return VP_OK;
 }
 
@@ -742,142 +705,141 @@ vp_status vp_ce_backward(const vp_problem* prob, const void* H, const void* cons
     if (misaligned(H) || misaligned(dH)) return VP_ERR_ALIGN;
   }
   hipStream_t s = (hipStream_t)stream;
-  FewPlan few;
-  if (few_plan(prob, &few))
-    return backward_few(prob, few, V, H, W_shards, targets, lse, grad_loss, dH, dW_shards, ws, s);
   unsigned long long* counter = (unsigned long long*)ws;
-  if (!vpce::run_ws_init(counter, s)) return VP_ERR_HIP;
   const bool accumulate = (prob->flags & VP_ACCUMULATE_DW) != 0;
   const int64_t d = prob->d;
 
   if (T == 0) {  // G is empty: dW = 0 (or unchanged when accumulating); dH has no rows
+    if (!vpce::run_ws_init(counter, s)) return VP_ERR_HIP;
     if (!accumulate)
       for (int q = 0; q < prob->P; ++q)
         if (!vpce::run_fill_zero(dW_shards[q], prob->shard_rows[q] * d, s)) return VP_ERR_HIP;
     return VP_OK;
   }
-  if (!vpce::run_count_bad(targets, T, V, prob->ignore_index, counter, s)) return VP_ERR_HIP;
-
-  const vpce::TileShape ts = vpce::tile_shape(prob->dtype);
-  const StripPlan plan = strip_plan(prob);
-  char* wsb = (char*)ws;
-  void* Ht = wsb + plan.off_ht;
-  void* Wt = wsb + plan.off_wt;
+  BwdPlan f = plan_bwd(prob);
+  cut_strips(prob, &f);
+  if (f.off_yt + align256((size_t)T * 4) > ws_bytes) return VP_ERR_WORKSPACE;
+  const vpce::BwdTile ft = vpce::bwd_tile(prob->dtype, f.cls);
   const size_t eb = elem_bytes(prob->dtype);
-  // The workspaces (the residual strips, H^T and W^T) are k-blocked in 128-byte
-  // blocks of KB elements (64 bfloat16, 32 float32): every k-slice of a 256-row
-  // tile the dH / dW contractions stream is one contiguous 32 KiB block.
-  const int64_t KB = ts.kblock;
-
-  {  // H^T [d][T_pad], k-blocked: [T_pad/KB][d][KB], zero beyond T
-    vpce::TransposeArgs tr;
-    tr.in = H;
-    tr.ld_in = d;
-    tr.out = Ht;
-    tr.R = (int32_t)T;
-    tr.C = (int32_t)d;
-    tr.R_pad = (int32_t)plan.T_pad;
-    if (!vpce::run_transpose(prob->dtype, tr, s)) return VP_ERR_HIP;
-  }
-
-  float* yt = (float*)(wsb + plan.off_yt);
+  const int64_t KB = vpce::tile_shape(prob->dtype).kblock;
+  char* wsb = (char*)ws;
+  float* yt = (float*)(wsb + f.off_yt);
+  float* part = f.max_jobs > 1 ? (float*)(wsb + f.off_part) : dH;
   {  // the target logit of every token, read by the residual tiles for the one-hot term
     vpce::TgtArgs ta;
     memset(&ta, 0, sizeof(ta));
     int32_t n_tiles = 0;
-    build_table(prob, W_shards, ts.grad_bm, &ta.st, &n_tiles);
+    build_table(prob, W_shards, ft.bm, &ta.st, &n_tiles);
     ta.H = H;
     ta.targets = targets;
     ta.T = T;
     ta.V = V;
     ta.d = (int32_t)d;
     ta.yt = yt;
+    ta.ignore_index = prob->ignore_index;
+    if (T <= kFewTokens) {
+      ta.count = counter;
+    } else if (!vpce::run_ws_init(counter, s) ||
+               !vpce::run_count_bad(targets, T, V, prob->ignore_index, counter, s)) {
+      return VP_ERR_HIP;
+    }
     if (!vpce::run_target_logits(prob->dtype, ta, s)) return VP_ERR_HIP;
   }
-
-  const std::vector<Chunk> chunks = strip_chunks(prob, plan);
+  auto copy_transposed = [&](const void* in, int64_t rows, void* out, int64_t rows_pad) {
+    vpce::TransposeArgs tr;
+    tr.in = in;
+    tr.ld_in = d;
+    tr.out = out;
+    tr.R = (int32_t)rows;
+    tr.C = (int32_t)d;
+    tr.R_pad = (int32_t)rows_pad;
+    return vpce::run_transpose(prob->dtype, tr, s);
+  };
+  if (f.cls == 3 && !copy_transposed(H, T, wsb + f.off_ht, round_up(T, 256))) return VP_ERR_HIP;
   int64_t off[VP_MAX_SHARDS];
   int64_t acc = 0;
   for (int q = 0; q < prob->P; ++q) {
     off[q] = acc;
     acc += prob->shard_rows[q];
   }
-  auto wchunk = [&](const Chunk& c) {
-    return (const char*)W_shards[c.q] + (size_t)c.v0 * d * eb;
+  auto segments = [&](const BwdStrip& st, vpce::StageSeg* out) {
+    for (size_t i = 0; i < st.segs.size(); ++i) {
+      const BwdStrip::Seg& sg = st.segs[i];
+      out[i].w = (const char*)W_shards[sg.q] + (size_t)(sg.v0 * d) * eb;
+      out[i].dw = dW_shards[sg.q] + sg.v0 * d;
+      out[i].gid0 = off[sg.q] + sg.v0;
+      out[i].rows = (int32_t)sg.rows;
+      out[i].row0 = (int32_t)sg.row0;
+    }
+    return (int32_t)st.segs.size();
   };
-  // Launch k runs the residual of strip k (into buffer k % 2) and the dH / dW
-  // contractions of strip k-1 (from buffer (k-1) % 2).  Stream order gives every
-  // dependency: strip k-1 was written by launch k-1; buffer k % 2 was last read
-  // by launch k-1; dH rows and dW chunks are only updated by consecutive launches.
-  const int64_t n = (int64_t)chunks.size();
+  // Launch k writes the residual of strip k (into buffer k % 2) and contracts strip
+  // k - 1 (from the other one).  Stream order gives every dependency: strip k - 1 was
+  // written by launch k - 1; buffer k % 2 was last read by launch k - 1; dH rows and dW
+  // chunks are only updated by consecutive launches.
+  const int64_t n_tc = ceil_div(T, f.Tc), n = (int64_t)f.strips.size() * n_tc;
   for (int64_t k = 0; k <= n; ++k) {
-    vpce::GradArgs g;
-    memset(&g, 0, sizeof(g));
+    vpce::StageArgs a;
+    memset(&a, 0, sizeof(a));
+    a.g.H = H;
+    a.g.targets = targets;
+    a.g.lse = lse;
+    a.g.grad = grad_loss;
+    a.g.strip = wsb + f.off_g[k % 2];
+    a.g.strip_t = wsb + f.off_gt[k % 2];
+    a.g.Tc = f.Tc;
+    a.g.Vc = f.Vr;
+    a.g.V = V;
+    a.g.ignore_index = prob->ignore_index;
+    a.g.yt = yt;
+    a.g.d = (int32_t)d;
     if (k < n) {
-      const Chunk& c = chunks[k];
-      g.W = wchunk(c);
-      g.H = H;
-      g.targets = targets;
-      g.lse = lse;
-      g.grad = grad_loss;
-      g.strip = wsb + plan.off_g[k % 2];
-      g.strip_t = wsb + plan.off_gt[k % 2];
-      g.Tc = plan.Tc;
-      g.Vc = plan.Vc;
-      g.t0 = c.t0;
-      g.gid0 = off[c.q] + c.v0;
-      g.V = V;
-      g.ignore_index = prob->ignore_index;
-      g.yt = yt;
-      g.M = (int32_t)c.M;
-      g.N = (int32_t)c.N;
-      g.d = (int32_t)d;
-      g.n_vt = (int32_t)ceil_div(c.M, ts.grad_bm);
+      const BwdStrip& st = f.strips[k / n_tc];
+      a.g.t0 = k % n_tc * f.Tc;
+      a.g.N = (int32_t)std::min(f.Tc, T - a.g.t0);
+      a.n_gseg = segments(st, a.gseg);
+      a.g.n_vt = (int32_t)(st.rows_pad / ft.bm);
     }
-    vpce::GemmArgs h, w;
-    memset(&h, 0, sizeof(h));
-    memset(&w, 0, sizeof(w));
+    int64_t longest = 0;
     if (k >= 1) {
-      const Chunk& c = chunks[k - 1];
-      if (c.new_vchunk) {  // W^T of this vocabulary chunk, k-blocked [Vc/KB][d][KB], zero beyond M
-        vpce::TransposeArgs tr;
-        tr.in = wchunk(c);
-        tr.ld_in = d;
-        tr.out = Wt;
-        tr.R = (int32_t)c.M;
-        tr.C = (int32_t)d;
-        tr.R_pad = (int32_t)round_up(c.M, KB);  // >= the K the dH launch reads
-        if (!vpce::run_transpose(prob->dtype, tr, s)) return VP_ERR_HIP;
+      const BwdStrip& st = f.strips[(k - 1) / n_tc];
+      a.c_t0 = (k - 1) % n_tc * f.Tc;
+      a.c_N = (int32_t)std::min(f.Tc, T - a.c_t0);
+      a.n_cseg = segments(st, a.cseg);
+      if (f.cls == 3) {
+        a.Ht = wsb + f.off_ht;
+        a.Wt = wsb + f.off_wt;
+        if (a.c_t0 == 0)  // the first strip of this vocabulary chunk
+          for (int i = 0; i < a.n_cseg; ++i)
+            if (!copy_transposed(a.cseg[i].w, a.cseg[i].rows,
+                                 wsb + f.off_wt + (size_t)(a.cseg[i].row0 * d) * eb,
+                                 round_up(a.cseg[i].rows, KB)))
+              return VP_ERR_HIP;
       }
-      // dH[t0 : t0+N] (+)= G^T W_chunk = G^T . (W^T)^T
-      h.A = wsb + plan.off_gt[(k - 1) % 2];
-      h.lda = KB;
-      h.kblka = plan.Tc * KB;
-      h.B = Wt;
-      h.ldb = KB;
-      h.kblkb = d * KB;
-      h.C = dH + c.t0 * d;
-      h.ldc = d;
-      h.M = (int32_t)c.N;
-      h.N = (int32_t)d;
-      h.K = (int32_t)round_up(c.M, ts.kalign);  // G^T and W^T are zero past M
-      h.beta = c.first_vchunk ? 0 : 1;
-      // dW_chunk (+)= G H[t0 : t0+N] = G . (H^T)^T
-      w.A = wsb + plan.off_g[(k - 1) % 2];
-      w.lda = KB;
-      w.kblka = plan.Vc * KB;
-      w.B = (const char*)Ht + (size_t)((c.t0 / KB) * d * KB) * eb;  // t0 is a multiple of Tc
-      w.ldb = KB;
-      w.kblkb = d * KB;
-      w.C = dW_shards[c.q] + c.v0 * d;
-      w.ldc = d;
-      w.M = (int32_t)c.M;
-      w.N = (int32_t)d;
-      w.K = (int32_t)round_up(c.N, ts.kalign);  // G is zero past N
-      w.beta = (c.t0 > 0 || accumulate) ? 1 : 0;
+      a.n_job = (int32_t)st.jobs.size();
+      for (size_t j = 0; j < st.jobs.size(); ++j) {
+        a.job[j] = st.jobs[j];
+        int64_t len = ceil_div(st.jobs[j].rows, KB);
+        if (st.jobs[j].n_seg > 1) {
+          len = 0;
+          for (int i = 0; i < st.jobs[j].n_seg; ++i) len += ceil_div(st.segs[st.jobs[j].seg + i].rows, KB);
+        }
+        longest = std::max(longest, len);
+      }
+      a.w_tiles = (int32_t)ceil_div(st.rows_pad, ft.bn);
+      a.G = wsb + f.off_g[(k - 1) % 2];
+      a.Gt = wsb + f.off_gt[(k - 1) % 2];
+      a.part = part;
+      a.part_stride = T * d;
+      a.beta_w = (a.c_t0 > 0 || accumulate) ? 1 : 0;
     }
-    if (!vpce::run_bwd_stage(prob->dtype, h, w, g, s)) return VP_ERR_HIP;
+    // the kinds with the longest sums first, so that the last round of tiles is short
+    const int64_t slices[3] = {longest, ceil_div(std::min(f.Tc, T), KB), ceil_div(d, KB)};
+    for (int i = 0; i < 3; ++i) a.order[i] = i;
+    std::sort(a.order, a.order + 3, [&](int x, int y) { return slices[x] > slices[y]; });
+    if (!vpce::run_stage(prob->dtype, f.cls, a, s)) return VP_ERR_HIP;
   }
+  if (f.max_jobs > 1 && !vpce::run_sum_parts(part, f.max_jobs, T * d, dH, s)) return VP_ERR_HIP;
   return VP_OK;
 }
 

@@ -103,23 +103,6 @@ struct TgtArgs {
   int64_t ignore_index;
 };
 
-// C[M][N] = (beta ? C : 0) + A B^T with A [M][K] (row stride lda) and B [N][K]
-// (row stride ldb), both k-contiguous.
-struct GemmArgs {
-  const void* A;
-  int64_t lda;
-  const void* B;
-  int64_t ldb;
-  float* C;
-  int64_t ldc;
-  int32_t M, N, K;
-  int32_t beta;
-  // elements between consecutive k-blocks (KB = 64 bfloat16 or 32 float32 wide)
-  // of A and of B: KB for a row-major operand, rows * KB for a k-blocked one
-  // (whose row pitch is KB)
-  int64_t kblka, kblkb;
-};
-
 // out[c][r] = in[r][c] for r < R (zero for R <= r < R_pad), c < C.  in is
 // row-major with pitch ld_in; out is k-blocked in 128-byte blocks of KB elements
 // (64 bfloat16, 32 float32), [R_pad/KB][C][KB] (element (c, r) at
@@ -140,38 +123,50 @@ struct TileShape {
 
 TileShape tile_shape(int dtype);
 
-// The backward on few tokens (at most one token chunk): a strip holds whole shards, or
-// one balanced piece of a large shard, and the dH tiles split its vocabulary rows into
-// jobs, each summing into a partial dH of its own.
+// One launch of the backward (stage_kernel): the residual tiles of strip k and the dH
+// and dW tiles of strip k - 1.  A strip is one token chunk of whole shards, or of one
+// balanced piece of a large shard: its segments, in visiting order, each starting at a
+// strip row that is a multiple of the residual tile's rows.  The dH tiles of a strip
+// run over all its segments, or are split into jobs along the vocabulary (where there
+// are few of them and their sums are long), each with a partial dH of its own.
 constexpr int kMaxSegs = 16, kMaxJobs = 32;
-struct FewSeg {  // one shard (piece) of a strip, in visiting order
+struct StageSeg {
   const void* w;   // its first row, [rows, d]
   float* dw;
-  int64_t gid0;    // global id of the first row
+  int64_t gid0;        // global id of the first row
   int32_t rows, row0;  // rows, and the strip row that the first of them has
 };
-struct FewJob {  // rows k0 .. k0 + rows - 1 of a segment (k0 in whole k-blocks)
-  int32_t seg, k0, rows, beta;
+// n_seg segments from `seg` on; one alone may be a part: rows k0 .. k0 + rows - 1 of it
+// (k0 in whole k-blocks).
+struct StageJob {
+  int32_t seg, n_seg, k0, rows, beta;
 };
-struct FewArgs {
-  GradArgs g;  // residual tiles; W, gid0, M are the segments'
-  FewSeg gseg[kMaxSegs], cseg[kMaxSegs];  // of the strip written and of the one contracted
-  FewJob job[kMaxJobs];
+struct StageArgs {
+  GradArgs g;  // residual tiles (W, gid0, M are the segments'); d, Tc, Vc of both strips
+  StageSeg gseg[kMaxSegs], cseg[kMaxSegs];  // of the strip written and of the one contracted
+  StageJob job[kMaxJobs];
   int32_t n_gseg, n_cseg, n_job;
-  int32_t g_tiles, w_tiles;  // residual row tiles of the strip written, dW ones of the other
-  int32_t order[3];          // kinds (0 dH, 1 dW, 2 residual) in launch order
-  int32_t beta_w;            // dW is added to
-  const void *G, *Gt;        // residual of the strip contracted
-  float* part;               // [jobs][T][d], or dH itself for one job
+  int32_t w_tiles;   // dW row tiles of the strip contracted
+  int32_t order[3];  // kinds (0 dH, 1 dW, 2 residual) in launch order
+  int32_t beta_w;    // dW is added to
+  int64_t c_t0;      // token chunk of the strip contracted
+  int32_t c_N;
+  const void *G, *Gt;  // its residual
+  const void *Wt, *Ht;  // class 3: k-blocked transposed copies of its W rows and of H
+  float* part;         // [jobs][T][d], or dH itself for one job
+  int64_t part_stride;
 };
-// tile class 0: 256 x 256 tiles; 1: 128 x 64 ones
-struct FewTile {
-  int bm, bn;   // residual tile: vocabulary rows by tokens; the contractions' tiles are
-                // bm columns of d by bn rows
-  double us;    // time per 128-byte slice of a tile, a CU to itself
+// Tile classes: 0 (bfloat16): 256 x 256 tiles; 1: 128 x 64 ones; 2: 128 x 128 ones, all of
+// them with W and H read transposed; 3: 256 x 256 tiles on transposed copies.
+constexpr int kBwdClasses = 4;
+struct BwdTile {
+  int bm, bn;    // residual tile: vocabulary rows by tokens; the contractions' tiles are
+                 // bm columns of d by bn rows
+  double us;     // time per 128-byte slice of a tile with every CU at work
 };
-FewTile few_tile(int dtype, int cls);
-bool run_few_stage(int dtype, int cls, const FewArgs& a, hipStream_t s);
+BwdTile bwd_tile(int dtype, int cls);
+int bwd_col_blocks(int cls, int d);  // column blocks of the contractions
+bool run_stage(int dtype, int cls, const StageArgs& a, hipStream_t s);
 // out[i] = sum over k < n of part[k * len + i], in the order of k; len % 4 == 0
 bool run_sum_parts(const float* part, int n, int64_t len, float* out, hipStream_t s);
 
@@ -204,10 +199,6 @@ struct StageSplit {
   int32_t cnt[3][8], first[3][8];
 };
 
-// One backward stage: the dH (h) and dW (w) tiles of one strip and the residual
-// tiles (g) of the next strip, in one launch.  A kind with M == 0 is absent.
-bool run_bwd_stage(int dtype, const GemmArgs& h, const GemmArgs& w, const GradArgs& g,
-                   hipStream_t s);
 bool run_transpose(int dtype, const TransposeArgs& a, hipStream_t s);
 bool run_target_logits(int dtype, const TgtArgs& a, hipStream_t s);
 

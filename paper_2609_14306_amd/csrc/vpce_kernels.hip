@@ -156,13 +156,18 @@ struct TrOperand {
   using S = typename E::storage;
   using F16 = typename E::frag16;
   static constexpr int ROW_BYTES = COLS * (int)sizeof(S);
-  static constexpr int CPR = ROW_BYTES / 16, RPL = 1024 / ROW_BYTES;  // k-rows per load
-  static_assert(ROW_BYTES >= 256 && ROW_BYTES <= 1024, "the swizzle needs two or four bank groups");
+  static constexpr int CPR = ROW_BYTES / 16;  // chunks per k-row
+  static_assert(ROW_BYTES % 128 == 0 && ROW_BYTES >= 256, "the swizzle needs two or four bank groups");
+  // Bank group (64 bytes) of k-row r's chunk 0 is r ROW_BYTES / 64 mod 4: 0 for every row
+  // where ROW_BYTES is a multiple of 256, alternating with r otherwise (640).
   __device__ __forceinline__ static int swz(int k) {
-    return sizeof(S) == 2 ? 4 * (k & 3) : 8 * ((k >> 2) & 1);
+    if (sizeof(S) == 4) return 8 * ((k >> 2) & 1);
+    return ROW_BYTES % 256 == 0 ? 4 * (k & 3) : 4 * ((k >> 1) & 1);
   }
-  __device__ __forceinline__ static int row(int q, int wave, int lane) {
-    return (wave + q * NWAVES) * RPL + lane / CPR;
+  // Chunk (wave + q NWAVES) * 64 + lane of the slice, row by row, is what this lane loads
+  // with load q: its k-row and its place in the row.
+  __device__ __forceinline__ static int place(int q, int wave, int lane) {
+    return (wave + q * NWAVES) * 64 + lane;
   }
   // Byte offset, from the slice's first row, of the chunk that this lane loads with
   // load q: k-row min(row, last), column chunk clamped to the last one below `cols`
@@ -170,7 +175,7 @@ struct TrOperand {
   // zeros of the other operand).
   __device__ __forceinline__ static uint32_t offset(int q, int wave, int lane, int64_t ld, int cols,
                                                     int last) {
-    const int r = row(q, wave, lane), c = (lane % CPR) ^ swz(r);
+    const int u = place(q, wave, lane), r = u / CPR, c = (u % CPR) ^ swz(r);
     return (uint32_t)(min(r, last) * ld * (int64_t)sizeof(S)) + 16u * (uint32_t)min(c, cols / E::VEC - 1);
   }
   // Lane's byte offset of the fragment of 32-wide block n0 at sub-step 0, and the read.
@@ -204,6 +209,10 @@ struct TrOperand {
 // the slice depth.
 // ATR_: A is [K][lda] with its rows along the contraction, read transposed (TrOperand);
 // K is its number of rows, any number, and B is whole slices that hold zeros past K.
+// run() with a `sum`: the accumulators are added to it and cleared every kFlush slices,
+// and left with what has gathered since (float32: a chain of 1024 products rounds less
+// than one of 25000, whose error shows in dH).
+constexpr int kFlush = 32;
 template <int BM_, int BN_, int WGM_, int WGN_, int BK_ = 64, int STAGES_ = 2, class E = Bf16,
           bool KTAIL_ = false, bool ATR_ = false>
 struct GemmDma {
@@ -211,9 +220,9 @@ struct GemmDma {
   using F16 = typename E::frag16;
   static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_;
   static constexpr int NT = 64 * WGM * WGN, NWAVES = WGM * WGN;
-  // One workgroup per CU (the ring takes 128 to 160 KiB of LDS): 512 threads run
-  // two wavefronts per SIMD with 256 registers each.
-  static constexpr int OCC = 1;
+  // Two wavefronts per SIMD with 256 registers each: one 512-thread workgroup per CU
+  // (whose ring takes 128 to 160 KiB of LDS) or two 256-thread ones.
+  static constexpr int OCC = NT == 512 ? 1 : 2;
   static constexpr int WM = BM / WGM, WN = BN / WGN, MB = WM / 32, NB = WN / 32;
   static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile must be whole 32x32 blocks");
   // BK_ sizes a slice row in bfloat16 units: 64 (128-byte rows) or 32 (64-byte rows)
@@ -237,7 +246,9 @@ struct GemmDma {
   // the loads of a slice go out in two halves, the larger first
   static constexpr int HALF0 = (NLOADS + 1) / 2, HALF1 = NLOADS - HALF0;
   static constexpr int NM = MB * NB, NR = MB + NB;   // MFMAs and fragment reads per sub-step
-  static_assert(NR <= NM && HALF0 <= (NM + 1) / 2, "interleave slots");
+  // one load per LSTEP MFMAs of a sub-step
+  static constexpr int LSTEP = 2 * HALF0 <= NM + 1 ? 2 : 1;
+  static_assert(NR <= NM && LSTEP * (HALF0 - 1) < NM, "interleave slots");
   static constexpr int LDS_ELEMS = STAGES * SLICE_BYTES / (int)sizeof(S);
   static_assert(STAGES * SLICE_BYTES <= 160 * 1024, "LDS");
 
@@ -356,6 +367,17 @@ struct GemmDma {
     }
   }
 
+  // sum += acc, acc = 0
+  __device__ __forceinline__ static void flush(f32x16_t (&acc)[MB][NB], f32x16_t (*sum)[NB]) {
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        sum[i][j] += acc[i][j];
+        acc[i][j] = f32x16_t{};
+      }
+  }
+
   // acc += A[m0 : m0+BM, 0:K] B[n0 : n0+BN, 0:K]^T; requires m0 < M and n0 < N.
   // Element (r, k) of A is at A[(k / KB) kblka + r lda + k % KB] with KB = E::KB
   // (row-major: kblka = KB; k-blocked: lda = KB, kblka = rows * KB), likewise for B.
@@ -367,7 +389,8 @@ struct GemmDma {
   __device__ __forceinline__ static void run(f32x16_t (&acc)[MB][NB], const S* __restrict__ A,
                                              int64_t lda, int m0, int M, const S* __restrict__ B,
                                              int64_t ldb, int n0, int N, int K, S* smem,
-                                             int64_t kblka = E::KB, int64_t kblkb = E::KB) {
+                                             int64_t kblka = E::KB, int64_t kblkb = E::KB,
+                                             f32x16_t (*sum)[NB] = nullptr) {
     // The wave index is made scalar so that every branch on it is a scalar branch.
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -463,11 +486,12 @@ struct GemmDma {
           __builtin_amdgcn_sched_barrier(0);
           if (idx < NB) b[cur ^ 1][idx] = read_one(src, wm, wn, skk, lane, MB + idx);
           if (jj == NB - 1 && live) a[i] = read_a(src, skk, i);
-          if ((idx & 1) == 0 && idx / 2 < dn && (kk == NKK - 1 || kk == 0) && dvalid)
-            issue_one(L, dslice, dq0 + idx / 2, lds0, wave);
+          if (idx % LSTEP == 0 && idx / LSTEP < dn && (kk == NKK - 1 || kk == 0) && dvalid)
+            issue_one(L, dslice, dq0 + idx / LSTEP, lds0, wave);
           __builtin_amdgcn_sched_barrier(0);
         }
       }
+      if (sum != nullptr && kt % kFlush == kFlush - 1) flush(acc, sum);
     }
     // no wave may still be reading the ring, nor a load writing it, when the caller
     // reuses LDS
@@ -565,13 +589,25 @@ struct Ring {
     }
   }
 
+  // sum += acc, acc = 0
+  __device__ __forceinline__ static void flush(f32x16_t (&acc)[MB][NB], f32x16_t (*sum)[NB]) {
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        sum[i][j] += acc[i][j];
+        acc[i][j] = f32x16_t{};
+      }
+  }
+
   // One tile of its own (the interface of GemmDma::run): acc += A B^T.  A part slice at
   // the end reads zeros past K, or, with ATR, repeats A's last row against B's zeros.
   template <bool RAGGED = false>
   __device__ __forceinline__ static void run(f32x16_t (&acc)[MB][NB], const S* __restrict__ A,
                                              int64_t lda, int m0, int M, const S* __restrict__ B,
                                              int64_t ldb, int n0, int N, int K, S* smem,
-                                             int64_t kblka = E::KB, int64_t kblkb = E::KB) {
+                                             int64_t kblka = E::KB, int64_t kblkb = E::KB,
+                                             f32x16_t (*sum)[NB] = nullptr) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave_m(wave), wn = wave_n(wave);
@@ -621,6 +657,7 @@ struct Ring {
       if (loaded < nk) load_next();
       __builtin_amdgcn_sched_barrier(0);
       multiply(acc, (const char*)smem + slot * SLICE_BYTES, wm, wn, lane);
+      if (sum != nullptr && it % kFlush == kFlush - 1) flush(acc, sum);
       slot = slot + 1 == STAGES ? 0 : slot + 1;
     }
     wait_lgkmcnt0();
@@ -695,50 +732,53 @@ __global__ void fill_zero_kernel(float* p, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = 0.f;
 }
 
-// Folds column block j of a logits tile into this lane's running state.  Tiles past
-// the end of a shard mask their padded rows; full tiles (all but the last of each
-// shard) take the select-free loops.  Register r of row block i holds tile row
-// wm + 32 i + acc_row(r, lane) = wm + 4 (lane / 32) + (a constant), so the mask
-// compares that constant with one per-lane limit.
+// Folds a logits tile into this lane's running states, column block by column block.
+// Tiles past the end of a shard mask their padded rows; full tiles (all but the last of
+// each shard) take the select-free loops.  Register r of row block i holds tile row
+// wm + 32 i + acc_row(r, lane) = wm + 4 (lane / 32) + (a constant), so the mask compares
+// that constant with one per-lane limit.
 template <int MB, int NB>
-__device__ __forceinline__ void fold_column(const f32x16_t (&acc)[MB][NB], int j, bool full,
-                                            int lim, float& m_run, float& s_run) {
-  // The maximum is taken on the raw logits and scaled once: scaling by a positive
-  // constant is monotone under rounding, so this equals the maximum of the scaled
-  // values.
-  float tmax = -INFINITY;
-  if (full) {
+__device__ __forceinline__ void fold_tile(const f32x16_t (&acc)[MB][NB], bool full, int lim,
+                                          float (&m_run)[NB], float (&s_run)[NB]) {
 #pragma unroll
-    for (int i = 0; i < MB; ++i)
+  for (int j = 0; j < NB; ++j) {
+    // The maximum is taken on the raw logits and scaled once: scaling by a positive
+    // constant is monotone under rounding, so this equals the maximum of the scaled
+    // values.
+    float tmax = -INFINITY;
+    if (full) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, acc[i][j][r]);
-  } else {
+      for (int i = 0; i < MB; ++i)
 #pragma unroll
-    for (int i = 0; i < MB; ++i)
+        for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, acc[i][j][r]);
+    } else {
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
-        if (32 * i + 8 * (r >> 2) + (r & 3) < lim) tmax = fmaxf(tmax, acc[i][j][r]);
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (32 * i + 8 * (r >> 2) + (r & 3) < lim) tmax = fmaxf(tmax, acc[i][j][r]);
+    }
+    tmax *= kLog2e;
+    const float scale = tmax > m_run[j] ? __builtin_amdgcn_exp2f(m_run[j] - tmax) : 1.f;
+    m_run[j] = fmaxf(m_run[j], tmax);
+    float sum = 0.f;
+    if (full) {
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          sum += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][j][r], kLog2e, -m_run[j]));
+    } else {
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][j][r], kLog2e, -m_run[j]));
+          sum += (32 * i + 8 * (r >> 2) + (r & 3) < lim) ? e : 0.f;
+        }
+    }
+    s_run[j] = s_run[j] * scale + sum;
   }
-  tmax *= kLog2e;
-  const float scale = tmax > m_run ? __builtin_amdgcn_exp2f(m_run - tmax) : 1.f;
-  m_run = fmaxf(m_run, tmax);
-  float sum = 0.f;
-  if (full) {
-#pragma unroll
-    for (int i = 0; i < MB; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        sum += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][j][r], kLog2e, -m_run));
-  } else {
-#pragma unroll
-    for (int i = 0; i < MB; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][j][r], kLog2e, -m_run));
-        sum += (32 * i + 8 * (r >> 2) + (r & 3) < lim) ? e : 0.f;
-      }
-  }
-  s_run = s_run * scale + sum;
 }
 
 // Target gather of column block j: exactly one tile in the whole vocabulary holds a
@@ -746,7 +786,7 @@ __device__ __forceinline__ void fold_column(const f32x16_t (&acc)[MB][NB], int j
 // target's row in this wave's WM rows (outside them: not here).
 template <int MB, int NB>
 __device__ __forceinline__ void gather_target(const f32x16_t (&acc)[MB][NB], int j, int64_t rel,
-                                              int rows, int wm, int lane, float* y) {
+                                              int rows, int wm, int lane, float* y, int n) {
   if (rel >= 0 && rel < rows) {
     const int relw = (int)rel - wm;
     if (relw >= 0 && relw < 32 * MB) {
@@ -758,7 +798,7 @@ __device__ __forceinline__ void gather_target(const f32x16_t (&acc)[MB][NB], int
         for (int i = 0; i < MB; ++i)
 #pragma unroll
           for (int r = 0; r < 16; ++r) yv = (i == want_i && r == want_r) ? acc[i][j][r] : yv;
-        *y = yv;
+        y[n] = yv;
       }
     }
   }
@@ -851,12 +891,11 @@ __global__ void __launch_bounds__(G::NT, G::OCC) fwd_kernel(FwdArgs a) {
 
     const bool full = rows == BM;
     const int lim = rows - wm - 4 * (lane >> 5);
+    fold_tile<MB, NB>(acc, full, lim, m_run, s_run);
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      fold_column<MB, NB>(acc, j, full, lim, m_run[j], s_run[j]);
-      gather_target<MB, NB>(acc, j, tgt[j] - gid0, rows, wm, lane,
-                            a.y_tgt + n0 + wn + 32 * j + (lane & 31));
-    }
+    for (int j = 0; j < NB; ++j)
+      gather_target<MB, NB>(acc, j, tgt[j] - gid0, rows, wm, lane, a.y_tgt,
+                            n0 + wn + 32 * j + (lane & 31));
   }
   write_partials<G>(a, m_run, s_run, split, n0, (float*)smem);
 }
@@ -952,11 +991,11 @@ __global__ void __launch_bounds__(G::NT, G::OCC* G::NWAVES / 4) stream_fwd_kerne
       const int64_t gid0 = a.st.off[pos] + r0;
       const bool full = rows == BM;
       const int lim = rows - wm - 4 * (lane >> 5);
+      fold_tile<MB, NB>(acc, full, lim, m_run, s_run);
 #pragma unroll
       for (int j = 0; j < NB; ++j) {
-        fold_column<MB, NB>(acc, j, full, lim, m_run[j], s_run[j]);
-        gather_target<MB, NB>(acc, j, tgt[j] - gid0, rows, wm, lane,
-                              a.y_tgt + n0 + wn + 32 * j + (lane & 31));
+        gather_target<MB, NB>(acc, j, tgt[j] - gid0, rows, wm, lane, a.y_tgt,
+                              n0 + wn + 32 * j + (lane & 31));
 #pragma unroll
         for (int i = 0; i < MB; ++i) acc[i][j] = f32x16_t{};
       }
@@ -1335,43 +1374,31 @@ struct ColBlocks {
 };
 template <class GM, class GW>
 __host__ __device__ inline ColBlocks col_blocks(int N) {
-  static_assert(GW::BM > GM::BM && GW::BN == GM::BN, "the wide tile only widens C^T rows");
+  static_assert(GW::BM >= GM::BM && GW::BN == GM::BN, "the wide tile only widens C^T rows");
   const int full = N / GM::BM, rem = N % GM::BM;
-  if (full >= 1 && rem > 0 && rem <= GW::BM - GM::BM) return ColBlocks{full, true};
+  if (GW::BM > GM::BM && full >= 1 && rem > 0 && rem <= GW::BM - GM::BM) return ColBlocks{full, true};
   return ColBlocks{(N + GM::BM - 1) / GM::BM, false};
 }
 
-// One tile of C (+)= A B^T: rows m0 = mt * BN .. of C, columns n0 .. n0 + BM - 1.
-template <class E, class G, bool RAGGED = false>
-__device__ __forceinline__ void gemm_tile(const GemmArgs& a, int mt, int n0,
-                                          typename E::storage* smem) {
-  using S = typename E::storage;
+// Stores a tile of sums: rows m0 .. of C, columns n0 .. n0 + BM - 1, added to what C
+// holds if beta.
+template <class G, bool RAGGED>
+__device__ __forceinline__ void store_tile(const f32x16_t (&acc)[G::MB][G::NB], float* __restrict__ C,
+                                           int64_t ldc, int M, int N, int m0, int n0, bool beta) {
   constexpr int MB = G::MB, NB = G::NB;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = G::wave_m(wave), wn = G::wave_n(wave);
-  // The tile is computed transposed, C^T[n][m] = sum_k B[n][k] A[m][k]: accumulator
-  // rows run along n, so each lane's group of 4 registers holds 4 consecutive
-  // columns of one row of C and the epilogue moves 16 bytes per access.
-  const int m0 = mt * G::BN;
-  f32x16_t acc[MB][NB];
-#pragma unroll
-  for (int i = 0; i < MB; ++i)
-#pragma unroll
-    for (int j = 0; j < NB; ++j) acc[i][j] = f32x16_t{};
-  G::template run<RAGGED>(acc, (const S*)a.B, a.ldb, n0, a.N, (const S*)a.A, a.lda, m0, a.M, a.K, smem,
-                          a.kblkb, a.kblka);
   // The epilogue takes a lane's row of C a batch of IB row blocks at a time: all
   // old values of the batch (beta = 1) are loaded before the first sum is stored,
   // so the lane waits for memory once per batch rather than once per 16-byte chunk
   // (a store to C ahead of the next load of C would keep the two in order).  Only
   // a RAGGED tile has columns at or past N.
   constexpr int IB = MB <= 4 ? MB : (MB + 1) / 2;
-  const bool beta = a.beta != 0;
 #pragma unroll
   for (int j = 0; j < NB; ++j) {
     const int m = m0 + wn + 32 * j + (lane & 31);
-    if (m >= a.M) continue;
-    float* crow = a.C + (int64_t)m * a.ldc;
+    if (m >= M) continue;
+    float* crow = C + (int64_t)m * ldc;
 #pragma unroll
     for (int i0 = 0; i0 < MB; i0 += IB) {
       float4 old[IB][4];
@@ -1386,7 +1413,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, int mt, int n0,
           for (int q = 0; q < 4; ++q) {
             const int i = i0 + ii;
             const int n = n0 + wm + 32 * i + acc_row(4 * q, lane);  // n .. n+3; N % 4 == 0
-            if (i < MB && (!RAGGED || n < a.N)) old[ii][q] = *(const float4*)(crow + n);
+            if (i < MB && (!RAGGED || n < N)) old[ii][q] = *(const float4*)(crow + n);
           }
       }
 #pragma unroll
@@ -1395,7 +1422,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, int mt, int n0,
         for (int q = 0; q < 4; ++q) {
           const int i = i0 + ii;
           const int n = n0 + wm + 32 * i + acc_row(4 * q, lane);
-          if (i >= MB || (RAGGED && n >= a.N)) continue;
+          if (i >= MB || (RAGGED && n >= N)) continue;
           const float4 c = old[ii][q];
           *(float4*)(crow + n) = make_float4(acc[i][j][4 * q] + c.x, acc[i][j][4 * q + 1] + c.y,
                                              acc[i][j][4 * q + 2] + c.z, acc[i][j][4 * q + 3] + c.w);
@@ -1404,73 +1431,104 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, int mt, int n0,
   }
 }
 
-// One launch of the backward pipeline: the dH and dW tiles of strip c and
-// the residual tiles of strip c+1 (which writes the other strip buffer).  XCD x
-// runs cnt[0][x] dH tiles, then cnt[1][x] dW tiles, then cnt[2][x] residual
-// tiles (numbered from first[.][x]): every XCD gets an even share of each kind,
-// consecutive tiles of one kind stay on one XCD's L2, and the longest tiles go
+// One launch of the backward: the dH and dW tiles of one strip and the residual tiles of
+// the next (which writes the other strip buffer).  XCD x runs cnt[p][x] tiles of the kind
+// order[p], numbered from first[p][x], for p = 0, 1, 2: every XCD gets an even share of
+// each kind, consecutive tiles of one kind stay on one XCD's L2, and the longest tiles go
 // first so that the partly filled last round is made of the short ones.
-template <class E, class GL, class GM, class GW>
-__global__ void __launch_bounds__(GM::NT, GM::OCC)
-    bwd_stage_kernel(GemmArgs h, GemmArgs w, GradArgs g, StageSplit sp) {
-  static_assert(GL::NT == GM::NT && GW::NT == GM::NT, "one workgroup size for every tile kind");
+//
+// A strip may hold several shards, and dH may be split into jobs along the vocabulary (see
+// StageArgs).  A dH tile runs the mainloop once per segment of its job, into the same accumulators.
+// One dH or dW tile, rows m0 = mt * BN .. of C and columns n0 .. n0 + BM - 1, computed
+// transposed, C^T[n][m] = sum_k A[n][k] B[m][k]: accumulator rows run along n, so each
+// lane's group of 4 registers holds 4 consecutive columns of one row of C and the
+// epilogue moves 16 bytes per access.  A is W or H read transposed (GC::ATR), or its
+// k-blocked transposed copy.
+// EDGE: the tile reaches past column d, which its stores leave out; SKIP: and so far that
+// the waves skip the MFMAs of dead row blocks (RAGGED of the mainloop, whose branches
+// cost more than they save where few blocks are dead).
+template <class E, class GC, bool EDGE, bool SKIP>
+__device__ __forceinline__ void contract_tile(const StageArgs& a, bool is_dh, int job, int mt, int n0,
+                                              typename E::storage* smem) {
   using S = typename E::storage;
-  constexpr int LDS0 = GL::LDS_ELEMS > GM::LDS_ELEMS ? GL::LDS_ELEMS : GM::LDS_ELEMS;
-  constexpr int LDS = LDS0 > GW::LDS_ELEMS ? LDS0 : GW::LDS_ELEMS;
-  __shared__ __attribute__((aligned(16))) S smem[LDS];
-  const int xcd = blockIdx.x % 8;
-  int local = blockIdx.x / 8;
-  int mt, nt;
-  // dH (kind 0) and dW (kind 1) tiles (see col_blocks); a tile that reaches past the
-  // hidden width d runs ragged: the waves' row blocks past d do no MFMA work.
+  constexpr int64_t KB = E::KB;
+  const int64_t d = a.g.d, Tc = a.g.Tc;
+  // contraction rows r0 .. r0 + rows - 1 of the strip (dH) or of the tokens (dW)
+  // float32: two-level sums where the registers hold them; the 256-row tiles, whose do
+  // not, add every segment to C by itself
+  constexpr bool F32 = sizeof(S) == 4, TWO = F32 && GC::BM < 256;
+  f32x16_t sum[TWO ? GC::MB : 1][GC::NB];
+  if constexpr (TWO)
 #pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const GemmArgs& a = k == 0 ? h : w;
-    if (local < sp.cnt[k][xcd]) {
-      const ColBlocks cb = col_blocks<GM, GW>(a.N);
-      const int n_m = (a.M + GM::BN - 1) / GM::BN;
-      grouped_tile(sp.first[k][xcd] + local, n_m, cb.n, 4, mt, nt);
-      const int n0 = nt * GM::BM;
-      if (cb.wide && nt == cb.n - 1) {
-        if (n0 + GW::BM > a.N)
-          gemm_tile<E, GW, true>(a, mt, n0, smem);
-        else
-          gemm_tile<E, GW>(a, mt, n0, smem);
-      } else if (n0 + GM::BM > a.N) {
-        gemm_tile<E, GM, true>(a, mt, n0, smem);
-      } else {
-        gemm_tile<E, GM>(a, mt, n0, smem);
-      }
-      return;
+    for (int i = 0; i < GC::MB; ++i)
+#pragma unroll
+      for (int j = 0; j < GC::NB; ++j) sum[i][j] = f32x16_t{};
+  auto mainloop = [&](f32x16_t(&acc)[GC::MB][GC::NB], const void* direct, const void* copy, int64_t r0,
+                      int rows, const S* B, int64_t kblkb, int m0, int M) {
+    if constexpr (GC::ATR) {
+      GC::template run<SKIP>(acc, (const S*)direct, d, n0, (int)d, B, KB, m0, M, rows, smem, KB, kblkb,
+                             TWO ? sum : nullptr);
+      if constexpr (TWO) GC::flush(acc, sum);
     }
-    local -= sp.cnt[k][xcd];
+    else
+      GC::template run<SKIP>(acc, (const S*)copy + r0 / KB * d * KB, KB, n0, (int)d, B, KB, m0, M,
+                             (rows + (int)KB - 1) / (int)KB * (int)KB, smem, d * KB, kblkb);
+  };
+  f32x16_t acc[GC::MB][GC::NB];
+#pragma unroll
+  for (int i = 0; i < GC::MB; ++i)
+#pragma unroll
+    for (int j = 0; j < GC::NB; ++j) acc[i][j] = f32x16_t{};
+  if (is_dh) {
+    const StageJob jb = a.job[job];
+    const int m0 = mt * GC::BN;
+    for (int i = 0; i < jb.n_seg; ++i) {
+      const StageSeg& sg = a.cseg[jb.seg + i];
+      const int k0 = jb.n_seg == 1 ? jb.k0 : 0, rows = jb.n_seg == 1 ? jb.rows : sg.rows;
+      mainloop(acc, (const S*)sg.w + (int64_t)k0 * d, a.Wt, sg.row0 + k0, rows,
+               (const S*)a.Gt + (sg.row0 + k0) / KB * Tc * KB, Tc * KB, m0, a.c_N);
+      if (F32 && !TWO && i + 1 < jb.n_seg) {
+        store_tile<GC, EDGE>(acc, a.part + job * a.part_stride + a.c_t0 * d, d, a.c_N, (int)d, m0, n0,
+                             i > 0 || jb.beta != 0);
+#pragma unroll
+        for (int x = 0; x < GC::MB; ++x)
+#pragma unroll
+          for (int y = 0; y < GC::NB; ++y) acc[x][y] = f32x16_t{};
+      }
+    }
+    if constexpr (TWO) GC::flush(sum, acc);
+    store_tile<GC, EDGE>(acc, a.part + job * a.part_stride + a.c_t0 * d, d, a.c_N, (int)d, m0, n0,
+                         jb.beta != 0 || (F32 && !TWO && jb.n_seg > 1));
+  } else {
+    const int row = mt * GC::BN;
+    int q = 0;
+    while (q + 1 < a.n_cseg && row >= a.cseg[q + 1].row0) ++q;
+    const StageSeg& sg = a.cseg[q];
+    const int m0 = row - sg.row0;
+    if (m0 >= sg.rows) return;  // padding of the segment
+    mainloop(acc, (const S*)a.g.H + a.c_t0 * d, a.Ht, a.c_t0, a.c_N, (const S*)a.G + sg.row0 * KB,
+             a.g.Vc * KB, m0, sg.rows);
+    if constexpr (TWO) GC::flush(sum, acc);
+    store_tile<GC, EDGE>(acc, sg.dw, d, sg.rows, (int)d, m0, n0, a.beta_w != 0);
   }
-  const int n_tb = (g.N + GL::BN - 1) / GL::BN;
-  grouped_tile(sp.first[2][xcd] + local, g.n_vt, n_tb, 4, mt, nt);
-  grad_tile<E, GL>(g, mt, nt, smem);
 }
 
-// One launch of the few-token backward: the dH and dW tiles of one strip and the
-// residual tiles of the next, as in bwd_stage_kernel, with three differences.  The
-// contractions read W and H as they are, transposed on the way out of LDS (a few per
-// cent of the mainloop's rate, where copies of W^T would cost 0.38 ms for V = 201088,
-// d = 2880 whatever T is); a strip holds several shards where they are small; and dH,
-// which has few tiles and long sums here, is split into jobs along the vocabulary.
-template <class E, class GL, class GC>
-__global__ void __launch_bounds__(GC::NT, GC::OCC* GC::NT / 256) few_stage_kernel(FewArgs a, StageSplit sp) {
+template <class E, class GL, class GC, class GW>
+__global__ void __launch_bounds__(GC::NT, GC::OCC* GC::NT / 256) stage_kernel(StageArgs a, StageSplit sp) {
   static_assert(GL::NT == GC::NT && GL::BN == GC::BN && GL::BM == GC::BM, "one tile shape");
   using S = typename E::storage;
-  constexpr int LDS = GL::LDS_ELEMS > GC::LDS_ELEMS ? GL::LDS_ELEMS : GC::LDS_ELEMS;
+  constexpr int LDS0 = GL::LDS_ELEMS > GC::LDS_ELEMS ? GL::LDS_ELEMS : GC::LDS_ELEMS;
+  constexpr int LDS = LDS0 > GW::LDS_ELEMS ? LDS0 : GW::LDS_ELEMS;
   __shared__ __attribute__((aligned(16))) S smem[LDS];
   const int xcd = blockIdx.x % 8;
   int idx = blockIdx.x / 8, p = 0;
   while (p < 2 && idx >= sp.cnt[p][xcd]) idx -= sp.cnt[p++][xcd];
   idx += sp.first[p][xcd];
   const int kind = a.order[p];
-  const int n_tb = (a.g.N + GL::BN - 1) / GL::BN, n_nb = (a.g.d + GC::BM - 1) / GC::BM;
-  const int64_t d = a.g.d, Tc = a.g.Tc;
-  if (kind == 2) {  // token blocks of one row tile side by side: they share its W
-    const int row = idx / n_tb * GL::BM;
+  int mt, nt;
+  if (kind == 2) {
+    grouped_tile(idx, a.g.n_vt, (a.g.N + GL::BN - 1) / GL::BN, 4, mt, nt);
+    const int row = mt * GL::BM;
     int q = 0;
     while (q + 1 < a.n_gseg && row >= a.gseg[q + 1].row0) ++q;
     GradArgs g = a.g;
@@ -1479,50 +1537,31 @@ __global__ void __launch_bounds__(GC::NT, GC::OCC* GC::NT / 256) few_stage_kerne
     g.M = a.gseg[q].rows;
     const int64_t row0 = a.gseg[q].row0;
     g.strip = (S*)g.strip + row0 * E::KB;
-    g.strip_t = (S*)g.strip_t + row0 / E::KB * Tc * E::KB;
-    grad_tile<E, GL>(g, (row - (int)row0) / GL::BM, idx % n_tb, smem);
+    g.strip_t = (S*)g.strip_t + row0 / E::KB * g.Tc * E::KB;
+    grad_tile<E, GL>(g, mt - (int)row0 / GL::BM, nt, smem);
     return;
   }
-  GemmArgs h;
-  int mt, nt;
-  h.ldb = h.ldc = d;
-  h.lda = E::KB;
-  h.N = (int32_t)d;
-  h.kblkb = 0;
-  if (kind == 0) {
-    const int per = n_tb * n_nb;
-    const FewJob job = a.job[idx / per];
-    mt = idx % per % n_tb;
-    nt = idx % per / n_tb;
-    const FewSeg& sg = a.cseg[job.seg];
-    h.B = (const S*)sg.w + (int64_t)job.k0 * d;
-    h.A = (const S*)a.Gt + (int64_t)(sg.row0 + job.k0) / E::KB * Tc * E::KB;
-    h.kblka = Tc * E::KB;
-    h.C = a.part + (int64_t)(idx / per) * a.g.N * d;
-    h.M = a.g.N;
-    h.K = job.rows;
-    h.beta = job.beta;
-  } else {
-    const int row = idx / n_nb * GC::BN;
-    nt = idx % n_nb;
-    int q = 0;
-    while (q + 1 < a.n_cseg && row >= a.cseg[q + 1].row0) ++q;
-    const FewSeg& sg = a.cseg[q];
-    mt = (row - sg.row0) / GC::BN;
-    if (mt * GC::BN >= sg.rows) return;  // padding of the segment
-    h.B = a.g.H;
-    h.A = (const S*)a.G + (int64_t)sg.row0 * E::KB;
-    h.kblka = a.g.Vc * E::KB;
-    h.C = sg.dw;
-    h.M = sg.rows;
-    h.K = a.g.N;
-    h.beta = a.beta_w;
-  }
+  const ColBlocks cb = col_blocks<GC, GW>(a.g.d);
+  const int n_m = kind == 0 ? (a.c_N + GC::BN - 1) / GC::BN : a.w_tiles;
+  const int per = n_m * cb.n, job = kind == 0 ? idx / per : 0;
+  grouped_tile(idx - job * per, n_m, cb.n, 4, mt, nt);
   const int n0 = nt * GC::BM;
-  if (n0 + GC::BM > (int)d)
-    gemm_tile<E, GC, true>(h, mt, n0, smem);
+  const int cols = a.g.d - n0;  // live columns from n0 on
+  if constexpr (GW::BM > GC::BM) {
+    if (cb.wide && nt == cb.n - 1) {
+      if (cols < GW::BM)
+        contract_tile<E, GW, true, false>(a, kind == 0, job, mt, n0, smem);
+      else
+        contract_tile<E, GW, false, false>(a, kind == 0, job, mt, n0, smem);
+      return;
+    }
+  }
+  if (cols >= GC::BM)
+    contract_tile<E, GC, false, false>(a, kind == 0, job, mt, n0, smem);
+  else if (2 * cols > GC::BM)
+    contract_tile<E, GC, true, false>(a, kind == 0, job, mt, n0, smem);
   else
-    gemm_tile<E, GC>(h, mt, n0, smem);
+    contract_tile<E, GC, true, true>(a, kind == 0, job, mt, n0, smem);
 }
 
 __global__ void __launch_bounds__(256) sum_parts_kernel(const float4* __restrict__ part, int n,
@@ -1611,23 +1650,27 @@ template <> struct Cfg<Bf16> {
   using LogitsTail = GemmDma<256, 256, 2, 4, 64, 2, Bf16, true>;
   using Stream128 = Ring<256, 128, 4, 2, 3, Bf16>;  // forward on few tokens, see fwd_tile
   using Stream64 = Ring<128, 64, 4, 2, 6, Bf16>;
-  using FewC = GemmDma<256, 256, 2, 4, 64, 2, Bf16, false, true>;  // few-token backward
-  using FewLs = Ring<128, 64, 4, 2, 3, Bf16>;
-  using FewCs = Ring<128, 64, 4, 2, 3, Bf16, true>;
+  using Tr256 = GemmDma<256, 256, 2, 4, 64, 2, Bf16, false, true>;  // few-token backward
+  using Tr320 = GemmDma<320, 256, 2, 4, 64, 2, Bf16, false, true>;
+  using Res128 = GemmDma<128, 128, 2, 2, 64, 2, Bf16, true>;
+  using Tr128 = GemmDma<128, 128, 2, 2, 64, 2, Bf16, false, true>;
+  using Res128x64 = Ring<128, 64, 4, 2, 3, Bf16>;
+  using Tr128x64 = Ring<128, 64, 4, 2, 3, Bf16, true>;
   static constexpr int KALIGN = 64;  // K granularity the dH / dW launches need
 };
 template <> struct Cfg<F32> {
   // The same direct-to-LDS ring and 256 x 256 tiles: 32 float32 k values per slice,
   // four 32x32x2 f32 MFMAs per fragment pair.
   using Logits = GemmDma<256, 256, 2, 4, 64, 2, F32>;
-  using Mm = Logits;  // the dH / dW contractions
-  using MmWide = GemmDma<320, 256, 2, 4, 64, 2, F32>;
   using LogitsTail = GemmDma<256, 256, 2, 4, 64, 2, F32, true>;
   using Stream128 = Ring<256, 128, 4, 2, 3, F32>;
   using Stream64 = Ring<128, 64, 4, 2, 6, F32>;
-  using FewC = GemmDma<256, 256, 2, 4, 64, 2, F32, false, true>;
-  using FewLs = Ring<128, 64, 4, 2, 3, F32>;
-  using FewCs = Ring<128, 64, 4, 2, 3, F32, true>;
+  using Mm = Logits;
+  using MmWide = GemmDma<320, 256, 2, 4, 64, 2, F32>;
+  using Res128 = GemmDma<128, 128, 2, 2, 64, 2, F32, true>;
+  using Tr128 = GemmDma<128, 128, 2, 2, 64, 2, F32, false, true>;
+  using Res128x64 = Ring<128, 64, 4, 2, 3, F32>;
+  using Tr128x64 = Ring<128, 64, 4, 2, 3, F32, true>;
   static constexpr int KALIGN = 32;  // K granularity the dH / dW launches need
 };
 
@@ -1688,48 +1731,31 @@ static StageSplit split_stage(const int n_kind[3]) {
   return sp;
 }
 
-template <class E, class GL, class GM, class GW>
-static bool launch_stage_g(const GemmArgs& h, const GemmArgs& w, const GradArgs& g, hipStream_t s) {
-  auto tiles = [](const GemmArgs& a) {  // C^T tiles: column blocks along N, BN along M
-    return a.M > 0 ? ((a.M + GM::BN - 1) / GM::BN) * col_blocks<GM, GW>(a.N).n : 0;
-  };
-  int n_kind[3];
-  n_kind[0] = tiles(h);
-  n_kind[1] = tiles(w);
-  n_kind[2] = g.M > 0 ? g.n_vt * ((g.N + GL::BN - 1) / GL::BN) : 0;
-  const int n = n_kind[0] + n_kind[1] + n_kind[2];
-  if (n == 0) return true;
-  const StageSplit sp = split_stage(n_kind);
-  hipLaunchKernelGGL((bwd_stage_kernel<E, GL, GM, GW>), dim3((unsigned)n), dim3(GM::NT), 0, s, h,
-                     w, g, sp);
-  return launched_ok();
-}
-template <class E>
-static bool launch_stage(const GemmArgs& h, const GemmArgs& w, const GradArgs& g, hipStream_t s) {
-  using Mm = typename Cfg<E>::Mm;
-  using Wd = typename Cfg<E>::MmWide;
-  if (g.d % E::KB == 0)
-    return launch_stage_g<E, typename Cfg<E>::Logits, Mm, Wd>(h, w, g, s);
-  return launch_stage_g<E, typename Cfg<E>::LogitsTail, Mm, Wd>(h, w, g, s);
-}
-
-template <class E, class GL, class GC>
-static bool launch_few_g(const FewArgs& a, hipStream_t s) {
-  const int n_tb = (a.g.N + GL::BN - 1) / GL::BN, n_nb = (a.g.d + GC::BM - 1) / GC::BM;
-  const int tiles[3] = {a.n_job * n_tb * n_nb, a.w_tiles * n_nb, a.g_tiles * n_tb};
+template <class E, class GL, class GC, class GW = GC>
+static bool launch_stage_g(const StageArgs& a, hipStream_t s) {
+  const int n_tb = (a.g.N + GL::BN - 1) / GL::BN, n_cb = (a.c_N + GC::BN - 1) / GC::BN;
+  const int n_nb = col_blocks<GC, GW>(a.g.d).n;
+  const int tiles[3] = {a.n_job * n_cb * n_nb, a.w_tiles * n_nb, a.g.n_vt * n_tb};
   int n_kind[3], n = 0;
   for (int p = 0; p < 3; ++p) n += n_kind[p] = tiles[a.order[p]];
   if (n == 0) return true;
-  hipLaunchKernelGGL((few_stage_kernel<E, GL, GC>), dim3((unsigned)n), dim3(GC::NT), 0, s, a,
+  hipLaunchKernelGGL((stage_kernel<E, GL, GC, GW>), dim3((unsigned)n), dim3(GC::NT), 0, s, a,
                      split_stage(n_kind));
   return launched_ok();
 }
 template <class E>
-static bool launch_few(int cls, const FewArgs& a, hipStream_t s) {
+static bool launch_stage(int cls, const StageArgs& a, hipStream_t s) {
   using C = Cfg<E>;
-  if (cls == 1) return launch_few_g<E, typename C::FewLs, typename C::FewCs>(a, s);
-  if (a.g.d % E::KB == 0) return launch_few_g<E, typename C::Logits, typename C::FewC>(a, s);
-  return launch_few_g<E, typename C::LogitsTail, typename C::FewC>(a, s);
+  if (cls == 1) return launch_stage_g<E, typename C::Res128x64, typename C::Tr128x64>(a, s);
+  if (cls == 2) return launch_stage_g<E, typename C::Res128, typename C::Tr128>(a, s);
+  const bool whole = a.g.d % E::KB == 0;
+  if constexpr (sizeof(typename E::storage) == 2) {
+    if (cls == 0 && whole) return launch_stage_g<E, typename C::Logits, typename C::Tr256, typename C::Tr320>(a, s);
+    if (cls == 0) return launch_stage_g<E, typename C::LogitsTail, typename C::Tr256, typename C::Tr320>(a, s);
+  }
+  if (cls != 3) return false;
+  if (whole) return launch_stage_g<E, typename C::Logits, typename C::Mm, typename C::MmWide>(a, s);
+  return launch_stage_g<E, typename C::LogitsTail, typename C::Mm, typename C::MmWide>(a, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -1804,18 +1830,25 @@ FwdTile fwd_tile(int dtype, int kind) {
   return dtype == 1 ? fwd_tile_of<Bf16>(kind) : fwd_tile_of<F32>(kind);
 }
 
-template <class E>
-static FewTile few_tile_of(int cls) {
-  constexpr bool b16 = sizeof(typename E::storage) == 2;
-  using G0 = typename Cfg<E>::FewC;
-  using G1 = typename Cfg<E>::FewCs;
-  return cls ? FewTile{G1::BM, G1::BN, b16 ? 0.47 : 1.33} : FewTile{G0::BM, G0::BN, b16 ? 1.4 : 7.45};
+int bwd_col_blocks(int cls, int d) {
+  using B = Cfg<Bf16>;
+  return cls == 1   ? col_blocks<B::Tr128x64, B::Tr128x64>(d).n
+         : cls == 2 ? col_blocks<B::Tr128, B::Tr128>(d).n
+                    : col_blocks<B::Tr256, B::Tr320>(d).n;
 }
-FewTile few_tile(int dtype, int cls) {
-  return dtype == 1 ? few_tile_of<Bf16>(cls) : few_tile_of<F32>(cls);
+// The tiles have the same shapes for both types.
+BwdTile bwd_tile(int dtype, int cls) {
+  using B = Cfg<Bf16>;
+  const bool b16 = dtype == 1;
+  switch (cls) {
+    case 1: return BwdTile{B::Tr128x64::BM, B::Tr128x64::BN, b16 ? 0.34 : 1.0};
+    case 2: return BwdTile{B::Tr128::BM, B::Tr128::BN, b16 ? 0.55 : 1.88};
+    case 3: return BwdTile{B::Mm::BM, B::Mm::BN, b16 ? 1.38 : 6.9};
+  }
+  return BwdTile{B::Tr256::BM, B::Tr256::BN, 1.40};
 }
-bool run_few_stage(int dtype, int cls, const FewArgs& a, hipStream_t s) {
-  return dtype == 1 ? launch_few<Bf16>(cls, a, s) : launch_few<F32>(cls, a, s);
+bool run_stage(int dtype, int cls, const StageArgs& a, hipStream_t s) {
+  return dtype == 1 ? launch_stage<Bf16>(cls, a, s) : launch_stage<F32>(cls, a, s);
 }
 bool run_sum_parts(const float* part, int n, int64_t len, float* out, hipStream_t s) {
   const int64_t vecs = len / 4, blocks = std::min<int64_t>((vecs + 255) / 256, 2048);
@@ -1868,10 +1901,6 @@ bool run_count_bad(const int64_t* targets, int64_t T, int64_t V, int64_t ignore_
   hipLaunchKernelGGL(count_bad_kernel, dim3((unsigned)((T + 255) / 256)), dim3(256), 0, s, targets,
                      T, V, ignore_index, counter);
   return launched_ok();
-}
-bool run_bwd_stage(int dtype, const GemmArgs& h, const GemmArgs& w, const GradArgs& g,
-                   hipStream_t s) {
-  return dtype == 1 ? launch_stage<Bf16>(h, w, g, s) : launch_stage<F32>(h, w, g, s);
 }
 bool run_target_logits(int dtype, const TgtArgs& a, hipStream_t s) {
   if (a.T <= 0) return true;

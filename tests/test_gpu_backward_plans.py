@@ -1,7 +1,7 @@
-"""The backward on few tokens: token counts and widths around its tiles, several shards in one
-strip (ragged, and next to ones that keep a strip of their own), shards cut into pieces by a
-small strip budget, dH sums in one and in many jobs, and dW added to.  Whole gradients against
-the float64 oracle at the bars of helpers.py."""
+"""How the backward is cut: token counts and widths around its tiles, several shards in one
+strip (ragged, and next to ones that keep a strip of their own), shards cut into pieces and
+tokens into chunks by a small strip budget, dH sums in one and in many jobs, and dW added to.
+Whole gradients against the float64 oracle at the bars of helpers.py."""
 import numpy as np
 import pytest
 
@@ -20,7 +20,8 @@ CASES = [
     (200, 320, [2600, 900, 1100], [2, 0, 1], 256 * 1024),          # shards cut into pieces
     (257, 1000, [700, 3001], [1, 0], 0),                           # 256-wide tiles and remainders
     (1100, 520, [9000, 300, 5000], [0, 1, 2], 0),                  # large tiles
-    (2048, 264, [6000, 7000], [1, 0], 0),                          # the most tokens
+    (2048, 264, [6000, 7000], [1, 0], 0),
+    (700, 136, [300, 260], [1, 0], 256 * 2048),                    # joined shards, two token chunks
 ]
 
 
@@ -31,6 +32,17 @@ def test_few_token_gradients(name, T, d, rows, order, strip):
     inp = wl.resplit(inp, rows, order=order)
     g = wl.random_grad_loss(T, 59, "random")
     compare_all(inp, run_gpu(inp, g, strip_elems=strip), run_oracle(inp, g), f"{inp.dtype} T={T} d={d}")
+
+
+# Many tokens on transposed copies of W and H, with several shards in a strip: in float32 each
+# shard's sum is added to dH by itself.
+@pytest.mark.parametrize("name,T,d,rows", [(BF16, 20480, 512, [5120, 5119, 5110, 5000]),
+                                           (F32, 10240, 4096, [2560, 2500, 2559, 2560])])
+def test_many_tokens_on_joined_shards(name, T, d, rows):
+    inp = wl.make_inputs(name, T=T, d=d, V=sum(rows), P=1, seed=67)
+    inp = wl.resplit(inp, rows, order=[2, 0, 3, 1])
+    g = wl.random_grad_loss(T, 67, "random")
+    compare_all(inp, run_gpu(inp, g), run_oracle(inp, g), f"{inp.dtype} T={T} d={d}")
 
 
 @pytest.mark.parametrize("name", [F32, BF16])
