@@ -89,11 +89,14 @@ typedef struct {
 
 /* Workspace sizes in bytes for vp_ce_forward (*fwd_bytes) and vp_ce_backward
  * (*bwd_bytes); either output pointer may be NULL.  Host only, needs no device.
- * forward: per-token partial states of the vocabulary splits, O(T);
+ * forward: per-token partial states of the vocabulary splits, O(T) (up to 2048
+ * tokens the call may use more of them than it needs: a workspace with room for
+ * 32 splits, 8 bytes x 32 x T beside the header and T floats, is accepted too);
  * backward: the residual strip in two layouts, twice (one being written while
- * the other is contracted: 4 x strip_elems elements at most), H^T (T x d
- * elements, T rounded up to 256) and W^T of one vocabulary chunk (d x strip
- * columns).  Neither depends on V. */
+ * the other is contracted: 4 x strip_elems elements at most), and room for H^T
+ * (T x d elements, T rounded up to 256) and W^T of one vocabulary chunk (d x
+ * strip columns), which hold transposed copies, longer strips or partial sums of
+ * dH, whichever the call's plan takes.  Neither depends on V. */
 vp_status vp_ce_workspace_size(const vp_problem* prob, size_t* fwd_bytes, size_t* bwd_bytes);
 
 /* Forward (Sec. 3.2, Eq. of the online-softmax fold; Algorithm 2):
@@ -193,9 +196,11 @@ vp_status vp_ce_fold_finalize(const vp_problem* prob, const int64_t* targets, co
 
 /* How vp_ce_backward cuts a problem (host only, needs no device): the residual
  * strip is Tc tokens by at most Vc vocabulary rows; `strips` strips cover the
- * T x V residual (each shard cut into balanced vocabulary chunks, each chunk
- * meeting every token chunk), and the backward makes stage_launches = strips + 1
- * launches of its fused recompute / residual / dH / dW kernel (0 when T == 0). */
+ * T x V residual (a shard of more than Vc rows cut into balanced vocabulary
+ * chunks, smaller consecutive shards of at least 256 rows sharing a strip while
+ * they fit, each meeting every token chunk), and the backward makes
+ * stage_launches = strips + 1 launches of its fused recompute / residual / dH / dW
+ * kernel (0 when T == 0). */
 typedef struct {
   int64_t Tc;
   int64_t Vc;

@@ -73,8 +73,8 @@ inline bool misaligned(const void* ptr) { return ((uintptr_t)ptr & 15u) != 0; }
 //   them.
 int splits_for(const vp_problem* p) {
   const vpce::TileShape ts = vpce::tile_shape(p->dtype);
-  const int64_t tok_blocks = std::max<int64_t>(1, ceil_div(p->T, ts.fwd_bn));
-  const int64_t panel = (int64_t)ts.fwd_bn * p->d * (int64_t)elem_bytes(p->dtype);
+  const int64_t tok_blocks = std::max<int64_t>(1, ceil_div(p->T, ts.bn));
+  const int64_t panel = (int64_t)ts.bn * p->d * (int64_t)elem_bytes(p->dtype);
   const int64_t need = std::max<int64_t>(
       4, std::max(ceil_div(kCUs, tok_blocks), ceil_div(kCUs * panel, kPanelCacheBudget)));
   int s = 4;
@@ -166,10 +166,10 @@ StripPlan strip_plan(const vp_problem* p) {
   const vpce::TileShape ts = vpce::tile_shape(p->dtype);
   const int64_t budget = p->strip_elems > 0 ? p->strip_elems : kDefaultStrip;
   const int64_t T = std::max<int64_t>(p->T, 1);
-  const int64_t side = std::max<int64_t>(ts.grad_bn, round_down((int64_t)std::sqrt((double)budget), ts.grad_bn));
+  const int64_t side = std::max<int64_t>(ts.bn, round_down((int64_t)std::sqrt((double)budget), ts.bn));
   StripPlan s;
-  s.Tc = std::min<int64_t>(round_up(T, ts.grad_bn), round_up(ceil_div(T, ceil_div(T, side)), ts.grad_bn));
-  s.Vc = std::max<int64_t>(ts.grad_bm, std::min<int64_t>(round_down(budget / s.Tc, ts.grad_bm),
+  s.Tc = std::min<int64_t>(round_up(T, ts.bn), round_up(ceil_div(T, ceil_div(T, side)), ts.bn));
+  s.Vc = std::max<int64_t>(ts.bm, std::min<int64_t>(round_down(budget / s.Tc, ts.bm),
                                                         32768));
   s.T_pad = round_up(T, 256);
   const size_t eb = elem_bytes(p->dtype);

@@ -116,14 +116,13 @@ struct TransposeArgs {
 };
 
 struct TileShape {
-  int fwd_bm, fwd_bn, grad_bm, grad_bn;
-  int kalign;  // the dH / dW contractions are launched with K rounded up to this
+  int bm, bn;  // the large tile: vocabulary rows by tokens
   int kblock;  // elements of one 128-byte k-block of the backward workspaces
 };
 
 TileShape tile_shape(int dtype);
 
-// One launch of the backward (stage_kernel): the residual tiles of strip k and the dH
+// One launch of the backward (bwd_stage_kernel): the residual tiles of strip k and the dH
 // and dW tiles of strip k - 1.  A strip is one token chunk of whole shards, or of one
 // balanced piece of a large shard: its segments, in visiting order, each starting at a
 // strip row that is a multiple of the residual tile's rows.  The dH tiles of a strip

@@ -2,18 +2,17 @@
 // cross-entropy, forward with an online log-sum-exp fold and backward with
 // logits recompute (arXiv 2609.14306, Sec. 3.2 and the appendix on Ring-DTP).
 //
-// One MFMA GEMM mainloop, C[m][n] = sum_k A[m][k] B[n][k] with both operands
-// k-contiguous, serves the four contractions of the path:
+// One MFMA GEMM mainloop, C[m][n] = sum_k A[m][k] B[n][k], serves the four
+// contractions of the path:
 //   logits (forward and recompute)  C[v][t] = sum_k W[v][k]   H[t][k]
-//   dH                              C[t][n] = sum_v G^T[t][v] W^T[n][v]
-//   dW                              C[v][n] = sum_t G[v][t]   H^T[n][t]
-// The backward stores the softmax residual of a (vocabulary chunk, token
-// chunk) strip in both layouts (G and G^T) and uses transposed copies of H
-// (once per call) and of each vocabulary chunk of W, so that every operand is
-// staged k-contiguous and every MFMA fragment is one 16-byte LDS read (an
-// operand read through gfx950's LDS transpose read, two 8-byte reads per
-// fragment, costs the mainloop about 4% of its rate, more than the second
-// layout and the transposes cost).
+//   dH                              C[t][n] = sum_v G^T[t][v] W[v][n]
+//   dW                              C[v][n] = sum_t G[v][t]   H[t][n]
+// The backward stores the softmax residual of a (vocabulary chunk, token chunk) strip
+// in both layouts (G and G^T), k-contiguous for both contractions.  Their other operand,
+// W or H, has its contraction index as its row index: it is read through gfx950's LDS
+// transpose read (two 8-byte reads per fragment instead of one of 16, 1.5% of the
+// mainloop's rate), or, where tokens are many enough to pay for them, from k-contiguous
+// transposed copies (0.47 ms for V = 201088, d = 2880 whatever T is; plan_bwd).
 //
 // Logits are computed transposed (vocabulary rows, token columns) so that in the
 // MFMA accumulator layout every lane owns whole token columns: the online
@@ -503,7 +502,8 @@ struct GemmDma {
 
 // ---------------------------------------------------------------------------
 // Small tiles for problems whose 256 x 256 tiles would leave most of the chip idle or
-// be mostly padding: the same slices, swizzle and direct-to-LDS loads, but a ring of
+// be mostly padding (T = 40, d = 4096, V = 151936, forward: 1549 us with 32 workgroups of
+// 256 x 256 tiles, 310 with 256 of them, 234 with these: 5.3 TB/s of W): the same slices, swizzle and direct-to-LDS loads, but a ring of
 // STAGES slices of which all but one are in flight, and one plain loop over slices
 // (wait, barrier, refill, multiply).  What bounds these problems is the stream of W
 // from memory: a CU keeps (STAGES - 1) slices of it in flight, and the ring runs on
@@ -1514,7 +1514,7 @@ __device__ __forceinline__ void contract_tile(const StageArgs& a, bool is_dh, in
 }
 
 template <class E, class GL, class GC, class GW>
-__global__ void __launch_bounds__(GC::NT, GC::OCC* GC::NT / 256) stage_kernel(StageArgs a, StageSplit sp) {
+__global__ void __launch_bounds__(GC::NT, GC::OCC* GC::NT / 256) bwd_stage_kernel(StageArgs a, StageSplit sp) {
   static_assert(GL::NT == GC::NT && GL::BN == GC::BN && GL::BM == GC::BM, "one tile shape");
   using S = typename E::storage;
   constexpr int LDS0 = GL::LDS_ELEMS > GC::LDS_ELEMS ? GL::LDS_ELEMS : GC::LDS_ELEMS;
@@ -1650,13 +1650,18 @@ template <> struct Cfg<Bf16> {
   using LogitsTail = GemmDma<256, 256, 2, 4, 64, 2, Bf16, true>;
   using Stream128 = Ring<256, 128, 4, 2, 3, Bf16>;  // forward on few tokens, see fwd_tile
   using Stream64 = Ring<128, 64, 4, 2, 6, Bf16>;
-  using Tr256 = GemmDma<256, 256, 2, 4, 64, 2, Bf16, false, true>;  // few-token backward
+  // The backward's tile classes (StageArgs): 0: Logits, Tr256, Tr320; 1: Res128x64,
+  // Tr128x64; 2: Res128, Tr128; 3: Logits, Mm, MmWide.  Measured, backward alone (us,
+  // classes 0 / 1 / 2): bf16 T = 2048, d = 2880, V = 201088 6661 / 9770 / 8406 and T = 40,
+  // d = 1000, V = 32003 98 / 74 / 76; float32 T = 256, d = 256, V = 2048 153 / 47 / 62 and
+  // T = 2048, d = 2880, V = 50000 13961 / 13173 / 13273; class 3 against 0: bf16 T = 32768,
+  // d = 2880, V = 201088 96.3 against 97.1 ms, T = 4096 12.60 against 12.38 ms.
+  using Tr256 = GemmDma<256, 256, 2, 4, 64, 2, Bf16, false, true>;
   using Tr320 = GemmDma<320, 256, 2, 4, 64, 2, Bf16, false, true>;
   using Res128 = GemmDma<128, 128, 2, 2, 64, 2, Bf16, true>;
   using Tr128 = GemmDma<128, 128, 2, 2, 64, 2, Bf16, false, true>;
   using Res128x64 = Ring<128, 64, 4, 2, 3, Bf16>;
   using Tr128x64 = Ring<128, 64, 4, 2, 3, Bf16, true>;
-  static constexpr int KALIGN = 64;  // K granularity the dH / dW launches need
 };
 template <> struct Cfg<F32> {
   // The same direct-to-LDS ring and 256 x 256 tiles: 32 float32 k values per slice,
@@ -1671,7 +1676,6 @@ template <> struct Cfg<F32> {
   using Tr128 = GemmDma<128, 128, 2, 2, 64, 2, F32, false, true>;
   using Res128x64 = Ring<128, 64, 4, 2, 3, F32>;
   using Tr128x64 = Ring<128, 64, 4, 2, 3, F32, true>;
-  static constexpr int KALIGN = 32;  // K granularity the dH / dW launches need
 };
 
 static inline bool launched_ok() { return hipGetLastError() == hipSuccess; }
@@ -1739,7 +1743,7 @@ static bool launch_stage_g(const StageArgs& a, hipStream_t s) {
   int n_kind[3], n = 0;
   for (int p = 0; p < 3; ++p) n += n_kind[p] = tiles[a.order[p]];
   if (n == 0) return true;
-  hipLaunchKernelGGL((stage_kernel<E, GL, GC, GW>), dim3((unsigned)n), dim3(GC::NT), 0, s, a,
+  hipLaunchKernelGGL((bwd_stage_kernel<E, GL, GC, GW>), dim3((unsigned)n), dim3(GC::NT), 0, s, a,
                      split_stage(n_kind));
   return launched_ok();
 }
@@ -1787,27 +1791,9 @@ bool scratch_base(void** out) {
 
 // ---- entry points used by the host API (vpce_api.cpp) ----
 TileShape tile_shape(int dtype) {
-  static_assert(Cfg<Bf16>::Logits::BM == Cfg<Bf16>::LogitsTail::BM &&
-                    Cfg<Bf16>::Logits::BN == Cfg<Bf16>::LogitsTail::BN,
-                "both logits mainloops must share the tile shape");
-  static_assert(Cfg<F32>::Logits::BM == Cfg<F32>::LogitsTail::BM &&
-                    Cfg<F32>::Logits::BN == Cfg<F32>::LogitsTail::BN,
-                "both logits mainloops must share the tile shape");
-  static_assert(Cfg<Bf16>::KALIGN == Bf16::KB && Cfg<F32>::KALIGN == F32::KB,
-                "dH / dW contractions read whole k-blocks");
-  TileShape t;
-  if (dtype == 1) {
-    t.fwd_bm = t.grad_bm = Cfg<Bf16>::Logits::BM;
-    t.fwd_bn = t.grad_bn = Cfg<Bf16>::Logits::BN;
-    t.kalign = Cfg<Bf16>::KALIGN;
-    t.kblock = Bf16::KB;
-  } else {
-    t.fwd_bm = t.grad_bm = Cfg<F32>::Logits::BM;
-    t.fwd_bn = t.grad_bn = Cfg<F32>::Logits::BN;
-    t.kalign = Cfg<F32>::KALIGN;
-    t.kblock = F32::KB;
-  }
-  return t;
+  using L = Cfg<Bf16>::Logits;
+  static_assert(L::BM == Cfg<F32>::Logits::BM && L::BN == Cfg<F32>::Logits::BN, "one large tile");
+  return TileShape{L::BM, L::BN, dtype == 1 ? Bf16::KB : F32::KB};
 }
 
 // Microseconds a workgroup takes per 128-byte slice of one tile, measured on launches
