@@ -113,7 +113,8 @@ int64_t count_tiles(const vp_problem* p, int bm) {
 }
 
 // Tile kind and splits of a forward over the problem's shards with room for `slots`
-// partial states.  Above kFewTokens tokens the 256 x 256 tile with splits_for() splits.
+// partial states.  Above kFewTokens tokens the 256 x 256 tile with at most splits_for()
+// splits.
 // Below, the kind whose launch is estimated shortest: every workgroup runs
 // ceil(tiles / splits) tiles one after the other, the launch takes ceil(workgroups /
 // places on the chip) such turns, and a tile takes d / slice depth times the measured
@@ -128,7 +129,26 @@ struct FwdPlan {
 };
 FwdPlan plan_fwd(const vp_problem* p, int64_t slots) {
   FwdPlan best{0, splits_for(p)};
-  if (p->T > kFewTokens) return best;
+  if (p->T > kFewTokens) {
+    // Whole tiles on the 256 x 256 tile again: where splits_for's workgroups leave a last
+    // round mostly empty, fewer splits are taken if they save more than 3% of the turns
+    // (below the four that share panels, more than a fifth).  d = 2880, V = 201088, bf16:
+    // T = 2304, 28 splits instead of 32: 3.60 -> 2.33 ms; T = 9000, 7 instead of 8: 13.5 ->
+    // 8.0 ms; T = 12000, 5 instead of 8: 12.9 -> 10.9 ms.
+    const vpce::FwdTile t = vpce::fwd_tile(p->dtype, 0);
+    const int64_t blocks = ceil_div(p->T, t.bn), tiles = std::max<int64_t>(1, count_tiles(p, t.bm));
+    auto turns = [&](int64_t S) { return ceil_div(tiles, S) * ceil_div(blocks * S, kCUs); };
+    const int64_t base = turns(best.splits);
+    int64_t least = base * 97 / 100;
+    for (int S = best.splits - 1; S >= 2; --S) {
+      if (S == 3) least = std::min(least, base * 80 / 100);
+      if (turns(S) < least) {
+        best.splits = S;
+        least = turns(S);
+      }
+    }
+    return best;
+  }
   double best_time = 0;
   for (int kind = 0; kind < vpce::kFwdKinds; ++kind) {
     const vpce::FwdTile t = vpce::fwd_tile(p->dtype, kind);

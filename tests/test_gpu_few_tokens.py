@@ -97,3 +97,18 @@ def test_workspace_of_32_splits_is_enough():
     ref_loss, ref_lse = _oracle_forward(inp)
     assert_loss_close("bf16", loss.cpu().numpy(), ref_loss, "32 splits loss")
     assert_loss_close("bf16", lse.cpu().numpy(), ref_lse, "32 splits lse")
+
+
+# More than 2048 tokens, where a full last round takes fewer splits than the workspace has
+# room for, and more splits than tiles.
+@pytest.mark.parametrize("T,rows", [(2304, [9000, 4000]), (5000, [100, 3000]), (9000, [500])])
+@pytest.mark.parametrize("name", [F32, BF16])
+def test_forward_many_tokens(name, T, rows):
+    import paper_2609_14306_amd as vp
+
+    inp = _inputs(name, T, 64, rows, list(range(len(rows))))
+    H, Ws, t = to_device(inp)
+    loss, lse = vp.forward(H, Ws, t, inp.ignore_index, inp.order)
+    ref_loss, ref_lse = _oracle_forward(inp)
+    assert_loss_close(inp.dtype, loss.cpu().numpy(), ref_loss, f"{name} T={T} loss")
+    assert_loss_close(inp.dtype, lse.cpu().numpy(), ref_lse, f"{name} T={T} lse")
