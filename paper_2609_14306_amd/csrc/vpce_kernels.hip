@@ -693,7 +693,10 @@ __device__ __forceinline__ void grouped_tile(int logical, int n_m, int n_n, int 
 // ---------------------------------------------------------------------------
 // Online-softmax state merge in the base-2 domain (m is a running maximum of
 // y*log2(e), s = sum 2^(y*log2e - m)).  An empty state is (-inf, 0); merging two of
-// them stays empty.
+// them stays empty.  While logits are folded an empty state is (kNoLogit, 0): logits of
+// minus infinity (or whose scaled value overflows to it) then add 2^-inf = 0 to it, where
+// a running maximum of -inf would make them NaN or infinite.
+constexpr float kNoLogit = -3.402823466e38f;  // the lowest float32
 __device__ __forceinline__ void merge_state(float& m, float& s, float mo, float so) {
   const float M = fmaxf(m, mo);
   const float ref = M == -INFINITY ? 0.f : M;
@@ -836,7 +839,7 @@ __device__ __forceinline__ void write_partials(const FwdArgs& a, float (&m_run)[
         merge_state(m_run[j], s_run[j], red[(w2 * 2) * BN + c], red[(w2 * 2 + 1) * BN + c]);
       const int64_t n = n0 + c;
       if (n < a.T) {
-        a.m_part[(int64_t)split * a.T + n] = m_run[j];
+        a.m_part[(int64_t)split * a.T + n] = m_run[j] == kNoLogit ? -INFINITY : m_run[j];
         a.s_part[(int64_t)split * a.T + n] = s_run[j];
       }
     }
@@ -868,7 +871,7 @@ __global__ void __launch_bounds__(G::NT, G::OCC) fwd_kernel(FwdArgs a) {
   int64_t tgt[NB];
 #pragma unroll
   for (int j = 0; j < NB; ++j) {
-    m_run[j] = -INFINITY;
+    m_run[j] = kNoLogit;
     s_run[j] = 0.f;
     const int64_t n = n0 + wn + 32 * j + (lane & 31);
     tgt[j] = n < a.T ? a.targets[n] : -1;
@@ -921,7 +924,7 @@ __global__ void __launch_bounds__(G::NT, G::OCC* G::NWAVES / 4) stream_fwd_kerne
   int64_t tgt[NB];
 #pragma unroll
   for (int j = 0; j < NB; ++j) {
-    m_run[j] = -INFINITY;
+    m_run[j] = kNoLogit;
     s_run[j] = 0.f;
     const int64_t n = n0 + wn + 32 * j + (lane & 31);
     tgt[j] = n < a.T ? a.targets[n] : -1;
