@@ -204,10 +204,13 @@ def _check_inputs(prob: Problem, H, W_shards, targets):
 # and then the checks above say what is wrong.
 def _pointers(tensors, dtype, shape, dev: int):
     out = []
-    for t in tensors:
-        if t.dtype != dtype or t.shape != shape or not t.is_contiguous() or t.get_device() != dev:
-            return None
-        out.append(t.data_ptr())
+    try:
+        for t in tensors:
+            if t.dtype != dtype or t.shape != shape or not t.is_contiguous() or t.get_device() != dev:
+                return None
+            out.append(t.data_ptr())
+    except (AttributeError, TypeError):  # not a tensor
+        return None
     return out
 
 

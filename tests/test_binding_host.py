@@ -113,3 +113,15 @@ def test_fold_calls_refuse():
     with pytest.raises(ValueError, match="targets: dtype"):
         vp.vp_ce_fold_finalize(full, t.int(), torch.zeros(3 * T), torch.zeros(T), torch.zeros(T),
                                torch.zeros(256, dtype=torch.uint8))
+
+
+def test_fold_refuses_a_state_that_is_no_tensor(monkeypatch):
+    # On a GPU the state's pointer is taken after the other tensors passed the one-pass
+    # checks: here they are made to pass.
+    H, Ws, t = _inputs()
+    shard = vp.Problem(T, D, [7], vp.VP_BF16)
+    ws = torch.zeros(vp.vp_ce_workspace_size(shard)[0], dtype=torch.uint8)
+    monkeypatch.setattr(vp, "_call_pointers", lambda *a, **k: (0, [None], 0, [], None, None, 0, 0))
+    for state in (None, 3, [0.0] * (3 * T)):
+        with pytest.raises(ValueError, match="state: expected a torch.Tensor"):
+            vp.vp_ce_fold_shard(shard, 0, H, Ws[2], t, state, ws)
