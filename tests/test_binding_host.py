@@ -97,6 +97,69 @@ def test_backward_refuses(case):
     _refused(vp.vp_ce_backward, _bwd_args(**over), match)
 
 
+# On GPU tensors the checks are one pass that takes the pointers (_call_pointers); what it
+# answers None for goes to the checks above.  CPU tensors whose H says it is on a GPU take
+# that pass here (their device index is -1 like H's own).
+class _GpuLike(torch.Tensor):
+    is_cuda = property(lambda self: True)
+
+
+class _OtherGpu(torch.Tensor):
+    def get_device(self):
+        return 1
+
+
+def _pass(a):
+    H = a["H"]
+    per_token = (a["loss"], a["lse"]) if "loss" in a else (a["lse"], a["grad_loss"])
+    return vp._call_pointers(a["prob"], H.as_subclass(_GpuLike), a["W_shards"], a["targets"], per_token,
+                             a.get("dH"), a.get("dW_shards"), a["ws"])
+
+
+def test_one_pass_takes_the_pointers():
+    for a in (_fwd_args(), _bwd_args()):
+        h, w, t, v, g, gw, ws, n = _pass(a)
+        assert h == a["H"].data_ptr() and t == a["targets"].data_ptr()
+        assert list(w) == [x.data_ptr() or None for x in a["W_shards"]]
+        assert v == [x.data_ptr() for x in ((a["loss"], a["lse"]) if "loss" in a else (a["lse"], a["grad_loss"]))]
+        assert (ws, n) == (a["ws"].data_ptr(), a["ws"].numel())
+        if "dH" in a:
+            assert g == a["dH"].data_ptr() and list(gw) == [x.data_ptr() or None for x in a["dW_shards"]]
+        else:
+            assert g is None and gw is None
+
+
+@pytest.mark.parametrize("case", sorted(set(FWD_CASES) - {"small workspace", "host tensors"}))
+def test_one_pass_refuses_forward(case):  # (the library judges the workspace's size)
+    assert _pass(_fwd_args(**FWD_CASES[case][0])) is None
+
+
+@pytest.mark.parametrize("case", sorted(set(BWD_CASES) - {"small workspace", "host tensors"}))
+def test_one_pass_refuses_backward(case):
+    assert _pass(_bwd_args(**BWD_CASES[case][0])) is None
+
+
+def test_one_pass_refuses_other_forms():
+    bf = torch.bfloat16
+    z = torch.zeros
+    for over in (dict(H=z(T, D, dtype=bf).unsqueeze(0)), dict(targets=z(2 * T, dtype=torch.int64)[::2]),
+                 dict(W_shards=[z(D, 5, dtype=bf).t(), z(0, D, dtype=bf), z(7, D, dtype=bf)]),
+                 dict(W_shards=[z(5, D, dtype=bf), None, z(7, D, dtype=bf)]), dict(loss=z(T + 1)), dict(lse=None),
+                 dict(ws=_fwd_args()["ws"].as_subclass(_OtherGpu)), dict(loss=z(T).as_subclass(_OtherGpu)),
+                 dict(targets=[0] * T), dict(ws=z(1 << 20, dtype=torch.uint8)[::2]), dict(ws=7)):
+        assert _pass(_fwd_args(**over)) is None, over
+    for over in (dict(dH=z(T, D + 1)), dict(dW_shards=[z(D, 5).t(), z(0, D), z(7, D)]), dict(dW_shards=None),
+                 dict(dW_shards=[z(5, D), z(0, D), z(7, D + 1)])):
+        assert _pass(_bwd_args(**over)) is None, over
+    assert _pass(_fwd_args(H=z(T, D, dtype=bf))) is not None
+    x = z(T)
+    assert vp._pointers((x,), torch.float32, (T,), -1) == [x.data_ptr()]
+    assert vp._pointers((x,), torch.float32, (T,), 0) is None  # another device
+    assert vp._shard_pointers(_prob(), [z(5, D, dtype=bf), z(0, D, dtype=bf), z(7, D, dtype=bf)], bf, 1) is None
+    a = _fwd_args()
+    assert vp._call_pointers(a["prob"], a["H"], a["W_shards"], a["targets"], (a["loss"], a["lse"])) is None  # a CPU H
+
+
 def test_fold_calls_refuse():
     H, Ws, t = _inputs()
     shard = vp.Problem(T, D, [7], vp.VP_BF16)
