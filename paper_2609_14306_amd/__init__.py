@@ -272,6 +272,8 @@ def vp_ce_state_init(state, T: int, stream=None) -> None:
 
 def vp_ce_fold_shard(shard: Problem, id_offset: int, H, W_shard, targets, state, ws,
                      stream=None) -> None:
+    """Folds one vocabulary shard (``shard.P == 1``) into `state` in place; `id_offset` is the
+    global id of its first row."""
     import torch
     if shard.P != 1:
         raise ValueError("vp_ce_fold_shard: the shard problem must have P == 1")
@@ -282,17 +284,25 @@ def vp_ce_fold_shard(shard: Problem, id_offset: int, H, W_shard, targets, state,
         _need_ws(ws, vp_ce_workspace_size(shard)[0] if shard.shard_rows[0] > 0 else 0)
         _same_device(named + [("state", state), ("ws", ws)])
 
-    c = None if ws is None else _call_pointers(shard, H, (W_shard,), targets, (), ws=ws)
-    p_state = _pointers((state,), torch.float32, (3 * shard.T,), H.get_device()) if c is not None else None
-    if p_state is None:
+    st = _fold_status(shard, id_offset, H, W_shard, targets, state, ws, stream)
+    if st is None:
         refuse()
         raise ValueError("vp_ce_fold_shard: unsupported tensors")
-    h, w, t, _, _, _, p_ws, n_ws = c
-    st = load_library().vp_ce_fold_shard(ctypes.byref(shard.c), int(id_offset), h, w[0], t, p_state[0],
-                                         p_ws, n_ws, _stream(stream))
     if st == VP_ERR_WORKSPACE:
         refuse()
     _check(st, "vp_ce_fold_shard")
+
+
+def _fold_status(shard: Problem, id_offset: int, H, W_shard, targets, state, ws, stream=None) -> Optional[int]:
+    """The status of the library's call, or None where a tensor is not what it needs."""
+    import torch
+    c = None if ws is None else _call_pointers(shard, H, (W_shard,), targets, (), ws=ws)
+    p_state = _pointers((state,), torch.float32, (3 * shard.T,), H.get_device()) if c is not None else None
+    if p_state is None:
+        return None
+    h, w, t, _, _, _, p_ws, n_ws = c
+    return load_library().vp_ce_fold_shard(ctypes.byref(shard.c), int(id_offset), h, w[0], t, p_state[0],
+                                           p_ws, n_ws, _stream(stream))
 
 
 def vp_ce_fold_finalize(prob: Problem, targets, state, loss, lse, ws, stream=None) -> None:
@@ -440,6 +450,10 @@ def fold_shard(H, W_shard, id_offset: int, targets, state, ws=None) -> None:
     shard = problem_for(H, [W_shard])
     fwd_b, _ = vp_ce_workspace_size(shard)
     if ws is None or ws.numel() * ws.element_size() < fwd_b:
+        # the size asked for leaves room for more splits than the call needs at few tokens: a
+        # smaller workspace that the call accepts is used, and not replaced on every call
+        if ws is not None and _fold_status(shard, id_offset, H, W_shard, targets, state, ws) == VP_OK:
+            return
         ws = torch.empty(fwd_b, dtype=torch.uint8, device=H.device)
     vp_ce_fold_shard(shard, id_offset, H, W_shard, targets, state, ws)
 

@@ -47,7 +47,8 @@ def test_forward_few_tokens(name, d, rows, T):
     assert_loss_close(inp.dtype, lse.cpu().numpy(), ref_lse, f"{name} T={T} d={d} lse")
 
 
-# A wide hidden state, where 65..128 tokens take the 128-token tile.
+# A wide hidden state, where 65..128 tokens take the 128-token tile for the large shard in
+# float32 (bfloat16 shards run on it in test_gpu_tiles.py).
 @pytest.mark.parametrize("T", [65, 128])
 @pytest.mark.parametrize("name", [F32, BF16])
 def test_fold_128_token_tile(name, T):
@@ -97,6 +98,31 @@ def test_workspace_of_32_splits_is_enough():
     ref_loss, ref_lse = _oracle_forward(inp)
     assert_loss_close("bf16", loss.cpu().numpy(), ref_loss, "32 splits loss")
     assert_loss_close("bf16", lse.cpu().numpy(), ref_lse, "32 splits lse")
+
+
+def test_fold_keeps_a_workspace_of_32_splits():
+    # fold_shard allocates only where the workspace it is given is too small for the call.
+    import torch
+
+    import paper_2609_14306_amd as vp
+
+    T, rows = 40, [9000, 4000]
+    inp = _inputs(BF16, T, 512, rows, [0, 1])
+    H, Ws, t = to_device(inp)
+    a256 = lambda n: (n + 255) // 256 * 256
+    small = 256 + 2 * a256(32 * T * 4) + a256(T * 4)
+    assert small < vp.vp_ce_workspace_size(vp.problem_for(H, Ws[:1]))[0]
+    for nbytes, allocations in ((small, 0), (small - 1, 2)):
+        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        state = vp.new_state(T, "cuda")
+        before = torch.cuda.memory_stats()["allocation.all.allocated"]
+        vp.fold_shard(H, Ws[0], 0, t, state, ws)
+        vp.fold_shard(H, Ws[1], rows[0], t, state, ws)
+        assert torch.cuda.memory_stats()["allocation.all.allocated"] - before == allocations
+        loss, lse = vp.fold_finalize(t, state, rows, inp.ignore_index)
+        ref_loss, ref_lse = _oracle_forward(inp)
+        assert_loss_close("bf16", loss.cpu().numpy(), ref_loss, f"{nbytes} bytes loss")
+        assert_loss_close("bf16", lse.cpu().numpy(), ref_lse, f"{nbytes} bytes lse")
 
 
 # More than 2048 tokens, where a full last round takes fewer splits than the workspace has
