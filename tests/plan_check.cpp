@@ -1,8 +1,11 @@
-// Runs vp_ce_backward's host side on the CPU with the kernels replaced by recorders, on
-// random problems, and checks what it would have launched: that the residual tiles cover
-// every (vocabulary row, token) once, that the dW and dH contractions read each of them once,
-// after it was written and before its buffer is written again, that partial sums start from
-// beta = 0 and are all added up, and that every buffer lies inside the workspace.
+// Runs the host side of the forwards, the fold and vp_ce_backward on the CPU with the kernels
+// replaced by recorders, on random problems, and checks what it would have launched.
+// Backward: that the residual tiles cover every (vocabulary row, token) once, that the dW and
+// dH contractions read each of them once, after it was written and before its buffer is
+// written again, that partial sums start from beta = 0 and are all added up, and that every
+// buffer lies inside the workspace.  Forwards: that the tiles cover every shard, that the
+// partial states lie inside the workspace, for every workspace size that is accepted, and
+// that the merge reads as many of them as were written.
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
@@ -17,28 +20,32 @@ static std::vector<vpce::StageArgs> launches;
 static std::vector<vpce::TransposeArgs> copies;
 static std::vector<size_t> copies_before;  // copies made before launch k
 static int last_cls, summed;
+static std::vector<vpce::FwdArgs> fwds;
+static std::vector<vpce::CombArgs> combs;
+static std::vector<vpce::FoldArgs> folds;
+static char* const kScratch = (char*)(9ll << 44);
 
+// (the tiles' sizes and times are the built library's, which this program is linked with)
 namespace vpce {
-TileShape tile_shape(int dtype) {
-  return dtype == VP_BF16 ? TileShape{256, 256, 64} : TileShape{256, 256, 32};
+bool scratch_base(void** p) {
+  *p = kScratch;
+  return true;
 }
-FwdTile fwd_tile(int, int) { return FwdTile{256, 256, 1, 1.4, 1.8}; }
-BwdTile bwd_tile(int dtype, int cls) {  // the sizes of the kernels' tiles; any times will do
-  const bool b = dtype == VP_BF16;
-  return cls == 1 ? BwdTile{128, 64, b ? 0.34 : 1.0} : cls == 2 ? BwdTile{128, 128, b ? 0.55 : 1.88}
-                                                                  : BwdTile{256, 256, b ? 1.4 : 6.9};
-}
-int bwd_col_blocks(int cls, int d) {
-  const int bm = cls == 1 || cls == 2 ? 128 : 256, rem = d % bm;
-  return bm == 256 && d >= 256 && rem > 0 && rem <= 64 ? d / bm : (d + bm - 1) / bm;
-}
-bool scratch_base(void**) { return false; }
 bool run_ws_init(unsigned long long*, hipStream_t) { return true; }
 bool run_fill_zero(float*, int64_t, hipStream_t) { return true; }
-bool run_fwd(int, const FwdArgs&, hipStream_t) { return true; }
-bool run_comb(const CombArgs&, hipStream_t) { return true; }
+bool run_fwd(int, const FwdArgs& a, hipStream_t) {
+  fwds.push_back(a);
+  return true;
+}
+bool run_comb(const CombArgs& a, hipStream_t) {
+  combs.push_back(a);
+  return true;
+}
 bool run_state_init(float*, int64_t, hipStream_t) { return true; }
-bool run_fold_merge(const FoldArgs&, hipStream_t) { return true; }
+bool run_fold_merge(const FoldArgs& a, hipStream_t) {
+  folds.push_back(a);
+  return true;
+}
 bool run_fold_finalize(const FinArgs&, hipStream_t) { return true; }
 bool run_count_bad(const int64_t*, int64_t, int64_t, int64_t, unsigned long long*, hipStream_t) { return true; }
 bool run_target_logits(int, const TgtArgs&, hipStream_t) { return true; }
@@ -110,6 +117,7 @@ static bool check(const vp_problem& p, int64_t accumulate) {
   for (size_t k = 0; k < launches.size(); ++k) {
     const vpce::StageArgs& a = launches[k];
     const int64_t Tc = a.g.Tc, Vr = a.g.Vc, strip = Tc * Vr * eb;
+    CHECK(p.dtype != VP_BF16 || Tc <= strip_plan(&p).Tc);  // one chain per dW tile
     CHECK(Tc % ft.bn == 0 && Vr % ft.bm == 0 && a.g.d == d && Tc * Vr < (1ll << 31));
     CHECK(a.g.yt && inside(a.g.yt, T * 4));
     if (a.n_gseg) {
@@ -210,12 +218,116 @@ static bool check(const vp_problem& p, int64_t accumulate) {
   return true;
 }
 
+// What a forward launched: every token block meets every tile of every shard, in as many
+// splits as the merge reads, and the partial states lie side by side inside the workspace.
+// y: the target logits' place where it is not the workspace.
+static bool check_fwd_args(const vp_problem& p, const vpce::FwdArgs& a, const char* ws, int64_t bytes, const float* y) {
+  const vpce::FwdTile t = vpce::fwd_tile(p.dtype, a.kind);
+  CHECK(a.kind >= 0 && a.kind < vpce::kFwdKinds && a.T == p.T && a.d == p.d);
+  CHECK(a.n_tok_blocks == ceil_div(p.T, t.bn));
+  CHECK(a.n_splits >= 1 && (a.kind == 0 || a.n_splits <= a.n_tiles));
+  CHECK((int64_t)a.n_tok_blocks * a.n_splits < (1ll << 31) / 512);  // threads of the grid
+  int64_t tiles = 0;
+  for (int i = 0; i < a.st.P; ++i) {
+    CHECK(a.st.tile0[i] == tiles);
+    tiles += ceil_div(a.st.rows[i], t.bm);
+  }
+  CHECK(tiles == a.n_tiles && a.st.tile0[a.st.P] == tiles);
+  const int64_t part = (int64_t)a.n_splits * p.T * 4;
+  const char *m = (const char*)a.m_part, *s = (const char*)a.s_part, *e = (const char*)(y ? y : a.y_tgt);
+  CHECK(m >= ws + kHeaderBytes && s >= m + part && s + part <= ws + bytes);
+  CHECK(a.y_tgt == (const float*)e && (y || (e >= s + part && e + p.T * 4 <= ws + bytes)));
+  return true;
+}
+
+static bool check_forward(const vp_problem& p) {
+  fwds.clear();
+  combs.clear();
+  folds.clear();
+  size_t bytes = 0;
+  CHECK(vp_ce_workspace_size(&p, &bytes, nullptr) == VP_OK);
+  char* ws = (char*)(1ll << 44);
+  const char* H = (const char*)(2ll << 44);
+  float *loss = (float*)(6ll << 44), *lse = (float*)(7ll << 44), *state = (float*)(8ll << 44);
+  const int64_t* targets = (const int64_t*)64;
+  std::vector<const void*> W(p.P);
+  for (int q = 0; q < p.P; ++q) W[q] = (const void*)((4ll << 44) + ((int64_t)q << 38));
+  // the least that was ever asked for: at most 32 splits, and one byte less is refused
+  const size_t least = fwd_ws_min(&p);
+  CHECK(least <= bytes && least <= kHeaderBytes + 2 * align256(32 * p.T * 4) + align256(p.T * 4));
+  CHECK(vp_ce_forward(&p, H, W.data(), targets, loss, lse, ws, least - 1, nullptr) == VP_ERR_WORKSPACE && fwds.empty());
+  for (size_t n : {least, (least + bytes) / 2, bytes, bytes + (1 << 20)}) {
+    CHECK(vp_ce_forward(&p, H, W.data(), targets, loss, lse, ws, n, nullptr) == VP_OK);
+    const vpce::FwdArgs& a = fwds.back();
+    const vpce::CombArgs& c = combs.back();
+    CHECK(check_fwd_args(p, a, ws, (int64_t)n, nullptr));
+    CHECK(a.counter == (unsigned long long*)ws && c.bad_counter == a.counter);
+    CHECK(c.m_part == a.m_part && c.s_part == a.s_part && c.y_tgt == a.y_tgt && c.n_splits == a.n_splits && c.T == p.T);
+    if (n > bytes) CHECK(a.n_splits == fwds[fwds.size() - 2].n_splits);  // more room changes nothing
+  }
+  const vp_status st = vp_ce_forward_noalloc(&p, H, W.data(), targets, loss, lse, nullptr);
+  CHECK(st == (least > vpce::kScratchBytes ? VP_ERR_WORKSPACE : VP_OK));
+  if (st == VP_OK) CHECK(check_fwd_args(p, fwds.back(), kScratch, vpce::kScratchBytes, nullptr));
+  int64_t off = 0;
+  for (int q = 0; q < p.P; off += p.shard_rows[q++]) {
+    vp_problem one = p;
+    int64_t rows = p.shard_rows[q];
+    one.P = 1;
+    one.shard_rows = &rows;
+    one.order = nullptr;
+    CHECK(fwd_ws_min(&one) == least);
+    for (size_t n : {least, bytes}) {
+      const size_t before = fwds.size();
+      CHECK(vp_ce_fold_shard(&one, off, H, W[q], targets, state, ws, n, nullptr) == VP_OK);
+      CHECK(fwds.size() == before + (rows > 0) && folds.size() <= fwds.size());
+      if (rows == 0) continue;
+      const vpce::FwdArgs& a = fwds.back();
+      const vpce::FoldArgs& f = folds.back();
+      CHECK(check_fwd_args(one, a, ws, (int64_t)n, state + 2 * p.T));
+      CHECK(!a.counter && a.st.off[0] == off && a.n_splits <= a.n_tiles);
+      CHECK(f.m_part == a.m_part && f.s_part == a.s_part && f.n_splits == a.n_splits && f.T == p.T && f.state == state);
+    }
+  }
+  return true;
+}
+
+// plan DTYPE T D STRIP ROWS...: the tiles that a problem runs on
+static int print_plan(int argc, char** argv) {
+  vp_problem p;
+  memset(&p, 0, sizeof(p));
+  p.dtype = atoi(argv[0]);
+  p.T = atoll(argv[1]);
+  p.d = atoll(argv[2]);
+  p.strip_elems = atoll(argv[3]);
+  std::vector<int64_t> rows;
+  for (int i = 4; i < argc; ++i) rows.push_back(atoll(argv[i]));
+  p.P = (int)rows.size();
+  p.shard_rows = rows.data();
+  if (validate(&p, nullptr) != VP_OK) return 1;
+  BwdPlan f = plan_bwd(&p);
+  cut_strips(&p, &f);
+  size_t most = 0;
+  for (const BwdStrip& st : f.strips) most = std::max(most, st.segs.size());
+  const FwdPlan w = plan_fwd(&p, partial_slots(&p));
+  printf("class %d Tc %lld Vc %lld strips %d segs %d jobs %d kind %d splits %d", f.cls, (long long)f.Tc, (long long)f.Vc,
+         (int)f.strips.size(), (int)most, f.max_jobs, w.kind, w.splits);
+  for (int64_t r : rows) {  // each shard folded by itself
+    vp_problem one = p;
+    one.P = 1;
+    one.shard_rows = &r;
+    printf(" fold %d", r > 0 ? plan_fwd(&one, partial_slots(&one)).kind : -1);
+  }
+  printf("\n");
+  return 0;
+}
+
 int main(int argc, char** argv) {
+  if (argc > 6 && !strcmp(argv[1], "plan")) return print_plan(argc - 2, argv + 2);
   std::mt19937_64 r(argc > 1 ? atoi(argv[1]) : 1);
   auto log_int = [&](double lo, double hi) {
     return (int64_t)exp(std::uniform_real_distribution<double>(log(lo), log(hi))(r));
   };
-  int classes[4] = {0, 0, 0, 0}, jobs = 0, joined = 0;
+  int classes[4] = {0, 0, 0, 0}, kinds[vpce::kFwdKinds] = {0}, jobs = 0, joined = 0, fewer = 0;
   for (int n = 0; n < 600; ++n) {
     vp_problem p;
     memset(&p, 0, sizeof(p));
@@ -239,7 +351,7 @@ int main(int argc, char** argv) {
     p.shard_rows = rows.data();
     p.order = order.data();
     p.ignore_index = -100;
-    if (!check(p, r() % 2)) {
+    if (!check(p, r() % 2) || !check_forward(p)) {
       printf("T=%lld d=%lld P=%d dtype=%d strip=%lld class=%d rows:", (long long)p.T, (long long)p.d, p.P, p.dtype,
              (long long)p.strip_elems, last_cls);
       for (auto x : rows) printf(" %lld", (long long)x);
@@ -247,12 +359,18 @@ int main(int argc, char** argv) {
       return 1;
     }
     ++classes[last_cls];
+    for (const auto& a : fwds) {
+      ++kinds[a.kind];
+      fewer += p.T > kFewTokens && a.st.P == p.P && a.n_splits < splits_for(&p);
+    }
     for (const auto& a : launches) {
       jobs += a.n_job > 1;
       joined += a.n_cseg > 1;
     }
   }
-  printf("classes %d %d %d %d, launches with several jobs %d, with joined shards %d\n", classes[0], classes[1],
-         classes[2], classes[3], jobs, joined);
-  return classes[0] && classes[1] && classes[2] && classes[3] && jobs && joined ? 0 : 1;
+  printf("classes %d %d %d %d, launches with several jobs %d, with joined shards %d; kinds %d %d %d, fewer splits %d\n",
+         classes[0], classes[1], classes[2], classes[3], jobs, joined, kinds[0], kinds[1], kinds[2], fewer);
+  return classes[0] && classes[1] && classes[2] && classes[3] && jobs && joined && kinds[0] && kinds[1] && kinds[2] && fewer
+             ? 0
+             : 1;
 }
