@@ -62,8 +62,9 @@ def test_workspace_size_independent_of_V():
 
 
 def _forward_splits(T, d, dtype, shard_rows=(25136,) * 8):
-    """The forward's vocabulary split count S, read back from its workspace size:
-    256 header bytes, S partial maxima and sums per token, one target logit per token."""
+    """The vocabulary splits that the forward's workspace has room for, read back from its
+    size: 256 header bytes, S partial maxima and sums per token, one target logit per token.
+    (How many a call takes: test_plan_host.py.)"""
     fwd, _ = vp.vp_ce_workspace_size(_prob(T=T, d=d, dtype=dtype, shard_rows=list(shard_rows)))
     a256 = lambda x: (x + 255) // 256 * 256
     body = fwd - 256 - a256(T * 4)
@@ -73,7 +74,7 @@ def _forward_splits(T, d, dtype, shard_rows=(25136,) * 8):
 
 
 @pytest.mark.parametrize("T, d, dtype, S", [
-    (256, 256, vp.VP_F32, 32),        # one token block: splits fill the CUs, at most 32
+    (256, 256, vp.VP_F32, 32),        # one token block: 8192 partial states
     (4096, 2880, vp.VP_BF16, 16),     # 16 token blocks: 16 splits fill 256 CUs
     (32768, 2880, vp.VP_BF16, 4),     # at least 4: 32 concurrent tiles share 12 panels
     (16384, 7168, vp.VP_BF16, 8),     # 64 H panels of 3.7 MB would overflow the cache budget

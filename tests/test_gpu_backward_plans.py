@@ -18,8 +18,8 @@ CASES = [
     (129, 136, [256] * 20, list(range(20)), 0),                    # more shards than a strip takes
     (200, 264, [30000], [0], 0),                                   # one segment in many jobs
     (200, 320, [2600, 900, 1100], [2, 0, 1], 256 * 1024),          # shards cut into pieces
-    (257, 1000, [700, 3001], [1, 0], 0),                           # 256-wide tiles and remainders
-    (1100, 520, [9000, 300, 5000], [0, 1, 2], 0),                  # large tiles
+    (257, 1000, [700, 3001], [1, 0], 0),                           # few shards in several jobs
+    (1100, 520, [9000, 300, 5000], [0, 1, 2], 0),                  # large tiles (bfloat16)
     (2048, 264, [6000, 7000], [1, 0], 0),
     (700, 136, [300, 260], [1, 0], 256 * 2048),                    # joined shards, two token chunks
 ]

@@ -29,9 +29,8 @@ def test_tiny_f32_full_workload():
 @pytest.mark.parametrize("dtype_name", ["tiny_f32_T256_d256_V2048_P8", "bf16_T4096_d2880_V201088_P8"])
 def test_ragged_shards_and_tiles(dtype_name, d):
     # T, d and every shard length off the tile grid; an empty shard; a permuted order.
-    # The dH / dW column blocks of d: 200 and 448 end in a 256-wide block with 200 and
-    # 192 live rows; 320 and 576 end in a whole 320-wide block (the first is the only
-    # block); 544 ends in a 320-wide block with 288 live rows.
+    # Few tokens and rows: the 128 x 64 tiles, whose column blocks of d are 128 wide and end
+    # with 72, 64 or 32 live columns (the 256- and 320-wide blocks: test_gpu_tiles.py).
     inp = _case(dtype_name, T=333, d=d, V=1100, P=1, seed=3)
     inp = wl.resplit(inp, [100, 0, 257, 131, 612], order=[3, 0, 4, 1, 2])
     g = wl.random_grad_loss(inp.T, 3, "random")
@@ -64,10 +63,9 @@ def test_small_strip_forces_many_chunks():
 @pytest.mark.parametrize("d", [320, 200])
 def test_f32_small_strip_many_token_and_vocab_chunks(d):
     # float32 with a 256 x 256 residual strip: 700 tokens make three token chunks (the dW
-    # tiles of the second and third add into dW, and read H^T at a k-block offset of whole
-    # 32-wide blocks), every shard several vocabulary chunks, the residual stored at the
-    # Tc pitch.  d = 320 runs the direct-to-LDS logits tiles, d = 200 the register-staged
-    # ones.  Full dH and dW against the oracle at the float32 bar.
+    # tiles of the second and third add into dW), every shard several vocabulary chunks, the
+    # residual stored at the Tc pitch, on 128 x 64 tiles.  d = 320 is whole slices, d = 200
+    # ends in a part slice.  Full dH and dW against the oracle at the float32 bar.
     inp = _case("tiny_f32_T256_d256_V2048_P8", T=700, d=d, V=1900, P=1, seed=43)
     inp = wl.resplit(inp, [611, 0, 300, 989], order=[2, 3, 0, 1])
     g = wl.random_grad_loss(inp.T, 43, "random")
