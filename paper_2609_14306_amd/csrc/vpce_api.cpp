@@ -87,7 +87,8 @@ int splits_for(const vp_problem* p) {
 // smaller tiles (plan_fwd); the partial states it may write per call (splits x T) are
 // at least what 32 splits need, and otherwise the 64 Ki that 32 splits take at
 // kFewTokens, but no more than a quarter of the bytes of H itself (8 bytes each) or
-// 8 Ki, whichever is larger.  The count never falls as T grows.
+// 8 Ki, whichever is larger.  Up to kFewTokens the count never falls as T grows; above, it
+// falls where splits_for halves (122880 states at T = 3840, d = 256, and 61456 at 3841).
 constexpr int64_t kFewTokens = 2048;
 int64_t partial_slots(const vp_problem* p) {
   const int64_t T = p->T, base = (int64_t)splits_for(p) * T;
@@ -134,7 +135,11 @@ FwdPlan plan_fwd(const vp_problem* p, int64_t slots) {
     // round mostly empty, fewer splits are taken if they save more than 3% of the turns
     // (below the four that share panels, more than a fifth).  d = 2880, V = 201088, bf16:
     // T = 2304, 28 splits instead of 32: 3.60 -> 2.33 ms; T = 9000, 7 instead of 8: 13.5 ->
-    // 8.0 ms; T = 12000, 5 instead of 8: 12.9 -> 10.9 ms.
+    // 8.0 ms; T = 12000, 5 instead of 8: 12.9 -> 10.9 ms.  The turns also outweigh the cache
+    // budget of splits_for: at wide d fewer splits mean more H panels at once, and are still
+    // the fastest (ms, panels in MiB): bf16 T = 38494, d = 6912, V = 142765, 8 splits 64.8
+    // (108), 6 70.9 (145), 5 63.9 (176); bf16 T = 58208, d = 7104, V = 11195, 8 splits 8.1
+    // (111), 4 7.9 (222); f32 T = 25549, d = 5696, V = 25891, 16 splits 63.6 (89), 5 59.1 (289).
     const vpce::FwdTile t = vpce::fwd_tile(p->dtype, 0);
     const int64_t blocks = ceil_div(p->T, t.bn), tiles = std::max<int64_t>(1, count_tiles(p, t.bm));
     auto turns = [&](int64_t S) { return ceil_div(tiles, S) * ceil_div(blocks * S, kCUs); };
@@ -298,8 +303,9 @@ int64_t job_slices(int64_t ks, int64_t launch_work, int slots) {
 // tile for its ends) spread over the CUs and half of its longest tile for the last round,
 // or that tile alone; about 8 us of launch and fill; and 0.3 of the time its bytes take at
 // 5 TB/s, the part that does not hide behind the rest.  Fitted to backwards of T = 40 to
-// 2048 tokens, d = 256 to 4096, V = 2048 to 201088: classes 0 to 2 within 10 to 15%, and
-// the class it picks within 1% of the fastest one on average (10% at worst).
+// 2048 tokens, d = 256 to 4096, V = 2048 to 201088.  On 64 random problems (T = 40 to 65536,
+// d = 256 to 7168, every class timed) the class it picks took 1.4% longer than the fastest
+// one on average up to 2048 tokens (15% at worst) and 2.5% above (19%).
 double plan_time(const vp_problem* p, const BwdPlan& f) {
   constexpr int64_t kEnds = 2;
   const vpce::BwdTile ft = vpce::bwd_tile(p->dtype, f.cls);

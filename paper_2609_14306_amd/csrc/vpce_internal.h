@@ -157,7 +157,6 @@ struct StageArgs {
 };
 // Tile classes: 0 (bfloat16): 256 x 256 tiles; 1: 128 x 64 ones; 2: 128 x 128 ones, all of
 // them with W and H read transposed; 3: 256 x 256 tiles on transposed copies.
-constexpr int kBwdClasses = 4;
 struct BwdTile {
   int bm, bn;    // residual tile: vocabulary rows by tokens; the contractions' tiles are
                  // bm columns of d by bn rows

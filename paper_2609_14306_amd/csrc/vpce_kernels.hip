@@ -212,8 +212,7 @@ struct TrOperand {
 // and left with what has gathered since (float32: a chain of 1024 products rounds less
 // than one of 25000, whose error shows in dH).
 constexpr int kFlush = 32;
-template <int BM_, int BN_, int WGM_, int WGN_, int BK_ = 64, int STAGES_ = 2, class E = Bf16,
-          bool KTAIL_ = false, bool ATR_ = false>
+template <int BM_, int BN_, int WGM_, int WGN_, class E = Bf16, bool KTAIL_ = false, bool ATR_ = false>
 struct GemmDma {
   using S = typename E::storage;
   using F16 = typename E::frag16;
@@ -224,15 +223,12 @@ struct GemmDma {
   static constexpr int OCC = NT == 512 ? 1 : 2;
   static constexpr int WM = BM / WGM, WN = BN / WGN, MB = WM / 32, NB = WN / 32;
   static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile must be whole 32x32 blocks");
-  // BK_ sizes a slice row in bfloat16 units: 64 (128-byte rows) or 32 (64-byte rows)
-  static constexpr int STAGES = STAGES_;
-  static constexpr int ROW_BYTES = BK_ * 2;
-  static constexpr int BK = ROW_BYTES / (int)sizeof(S);  // k values per slice
-  static_assert((BK_ == 32 || BK_ == 64) && STAGES >= 2, "slice depth and ring slots");
-  static_assert(E::KB % BK == 0, "slices never straddle a k-block of the layout");
+  static constexpr int STAGES = 2;        // ring slots
+  static constexpr int ROW_BYTES = 128;
+  static constexpr int BK = E::KB;        // k values per slice: one k-block of the layout
   static constexpr bool KTAIL = KTAIL_, ATR = ATR_;
+  static constexpr bool SKIPS = true;             // run<true> skips dead row blocks
   static constexpr int NKK = ROW_BYTES / 32;      // sub-steps per slice (two 16-byte chunks each)
-  static_assert(NKK % 2 == 0, "register sets alternate per sub-step across slices");
   static constexpr int CPR = ROW_BYTES / 16;      // 16-byte chunks per row
   static constexpr int RPW = 256 / ROW_BYTES;     // rows per 64-bank (256-byte) window
   static constexpr int RPI = 1024 / ROW_BYTES;    // rows per 1 KiB load instruction
@@ -321,7 +317,6 @@ struct GemmDma {
         const char* p = q < A_LOADS
                             ? L.baseA + (k0 / KB) * L.kblkA * (int64_t)sizeof(S) + L.offA[q < A_LOADS ? q : 0]
                             : L.baseB + (k0 / KB) * L.kblkB * (int64_t)sizeof(S) + L.offB[q < A_LOADS ? 0 : q - A_LOADS];
-        static_assert(BK == KB, "the tail slice starts at a k-block");
         lds_dma16_lane(c < L.tail_chunks ? (const void*)p : (const void*)&zero_chunk, l);
         return;
       }
@@ -349,21 +344,13 @@ struct GemmDma {
     return *(const F16*)(slot + row * ROW_BYTES + ((chunk ^ key(row)) << 4));
   }
 
-  // Wait until at most n slices' loads (n in [0, STAGES - 1]) of this wave are in
-  // flight; loads return in issue order.
+  // Wait until at most n slices' loads (0 or 1) of this wave are in flight; loads return
+  // in issue order.
   __device__ __forceinline__ static void wait_slices(int n) {
-    if constexpr (STAGES == 2) {
-      if (n <= 0) wait_vmcnt<0>(); else wait_vmcnt<NLOADS>();
-    } else {
-      static_assert(STAGES <= 5, "wait_slices covers up to five slots");
-      switch (n) {
-        case 0: wait_vmcnt<0>(); break;
-        case 1: wait_vmcnt<NLOADS>(); break;
-        case 2: wait_vmcnt<2 * NLOADS>(); break;
-        case 3: wait_vmcnt<3 * NLOADS>(); break;
-        default: wait_vmcnt<4 * NLOADS>(); break;
-      }
-    }
+    if (n <= 0)
+      wait_vmcnt<0>();
+    else
+      wait_vmcnt<NLOADS>();
   }
 
   // sum += acc, acc = 0
@@ -455,11 +442,11 @@ struct GemmDma {
           src = ring + slot_bytes(kt);
           skk = kk + 1;
         } else {
-          // Slice kt+1 must have landed; slices kt+2 .. kt+STAGES-1 may still be
-          // in flight.  Taken on the last slice too (one spare barrier, fragments
-          // read from an idle slot and never used): no branch around the LDS
-          // reads, so the compiler's count of reads in flight stays exact.
-          wait_slices(min(STAGES - 2, nk - 2 - kt));
+          // Slice kt+1 must have landed; no other load is in flight.  Taken on the last
+          // slice too (one spare barrier, fragments read from an idle slot and never
+          // used): no branch around the LDS reads, so the compiler's count of reads in
+          // flight stays exact.
+          wait_vmcnt<0>();
           wait_lgkmcnt0();  // this wave's reads of slice kt
           __builtin_amdgcn_s_barrier();
           src = ring + slot_bytes(kt + 1);
@@ -502,12 +489,13 @@ struct GemmDma {
 
 // ---------------------------------------------------------------------------
 // Small tiles for problems whose 256 x 256 tiles would leave most of the chip idle or
-// be mostly padding (T = 40, d = 4096, V = 151936, forward: 1549 us with 32 workgroups of
-// 256 x 256 tiles, 310 with 256 of them, 234 with these: 5.3 TB/s of W): the same slices, swizzle and direct-to-LDS loads, but a ring of
+// be mostly padding: the same slices, swizzle and direct-to-LDS loads, but a ring of
 // STAGES slices of which all but one are in flight, and one plain loop over slices
 // (wait, barrier, refill, multiply).  What bounds these problems is the stream of W
 // from memory: a CU keeps (STAGES - 1) slices of it in flight, and the ring runs on
-// across tile boundaries (stream_fwd), so that no tile starts on an empty pipe.
+// across tile boundaries (stream_fwd_kernel), so that no tile starts on an empty pipe.
+// Forward of T = 40, d = 4096, V = 151936 in bfloat16: 1549 us with 32 workgroups of
+// 256 x 256 tiles, 310 with 256 of them, 234 with these (5.3 TB/s of W).
 // ATR_: A is read transposed, as in GemmDma.
 template <int BM_, int BN_, int WGM_, int WGN_, int STAGES_, class E, bool ATR_ = false>
 struct Ring {
@@ -524,7 +512,7 @@ struct Ring {
   static constexpr int A_LOADS = BM / 8 / NWAVES, B_LOADS = BN / 8 / NWAVES;
   static_assert(BM % (8 * NWAVES) == 0 && BN % (8 * NWAVES) == 0, "whole load groups per wave");
   static constexpr int NLOADS = A_LOADS + B_LOADS;
-  static constexpr bool ATR = ATR_;
+  static constexpr bool ATR = ATR_, SKIPS = false;
   static constexpr int LDS_ELEMS = LDS_BYTES / (int)sizeof(S);
   using TrA = TrOperand<E, BM, NWAVES>;
   static_assert(STAGES >= 3 && (STAGES - 2) * NLOADS < 64 && LDS_BYTES <= 160 * 1024, "ring");
@@ -608,6 +596,7 @@ struct Ring {
                                              int64_t ldb, int n0, int N, int K, S* smem,
                                              int64_t kblka = E::KB, int64_t kblkb = E::KB,
                                              f32x16_t (*sum)[NB] = nullptr) {
+    static_assert(!RAGGED, "one row block per wave: nothing to skip");
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave_m(wave), wn = wave_n(wave);
@@ -1363,8 +1352,6 @@ __global__ void count_bad_kernel(const int64_t* targets, int64_t T, int64_t V, i
   }
 }
 
-// One float32 output tile of C = (beta ? C : 0) + A B^T (a dH or a dW tile; N, the
-// hidden width, is a multiple of 4).
 // Column blocks of a dH / dW contraction, whose N is the hidden width d: BM-wide
 // tiles of C^T rows (GM), except that a remainder of at most GW::BM - GM::BM
 // columns joins the last full block, which then runs as one GW::BM-wide tile
@@ -1434,19 +1421,13 @@ __device__ __forceinline__ void store_tile(const f32x16_t (&acc)[G::MB][G::NB], 
   }
 }
 
-// One launch of the backward: the dH and dW tiles of one strip and the residual tiles of
-// the next (which writes the other strip buffer).  XCD x runs cnt[p][x] tiles of the kind
-// order[p], numbered from first[p][x], for p = 0, 1, 2: every XCD gets an even share of
-// each kind, consecutive tiles of one kind stay on one XCD's L2, and the longest tiles go
-// first so that the partly filled last round is made of the short ones.
-//
-// A strip may hold several shards, and dH may be split into jobs along the vocabulary (see
-// StageArgs).  A dH tile runs the mainloop once per segment of its job, into the same accumulators.
 // One dH or dW tile, rows m0 = mt * BN .. of C and columns n0 .. n0 + BM - 1, computed
 // transposed, C^T[n][m] = sum_k A[n][k] B[m][k]: accumulator rows run along n, so each
 // lane's group of 4 registers holds 4 consecutive columns of one row of C and the
 // epilogue moves 16 bytes per access.  A is W or H read transposed (GC::ATR), or its
-// k-blocked transposed copy.
+// k-blocked transposed copy.  A strip may hold several shards, and dH may be split into
+// jobs along the vocabulary (see StageArgs): a dH tile runs the mainloop once per segment
+// of its job, into the same accumulators.
 // EDGE: the tile reaches past column d, which its stores leave out; SKIP: and so far that
 // the waves skip the MFMAs of dead row blocks (RAGGED of the mainloop, whose branches
 // cost more than they save where few blocks are dead).
@@ -1516,6 +1497,11 @@ __device__ __forceinline__ void contract_tile(const StageArgs& a, bool is_dh, in
   }
 }
 
+// One launch of the backward: the dH and dW tiles of one strip and the residual tiles of
+// the next (which writes the other strip buffer).  XCD x runs cnt[p][x] tiles of the kind
+// order[p], numbered from first[p][x], for p = 0, 1, 2: every XCD gets an even share of
+// each kind, consecutive tiles of one kind stay on one XCD's L2, and the longest tiles go
+// first so that the partly filled last round is made of the short ones.
 template <class E, class GL, class GC, class GW>
 __global__ void __launch_bounds__(GC::NT, GC::OCC* GC::NT / 256) bwd_stage_kernel(StageArgs a, StageSplit sp) {
   static_assert(GL::NT == GC::NT && GL::BN == GC::BN && GL::BM == GC::BM, "one tile shape");
@@ -1561,9 +1547,9 @@ __global__ void __launch_bounds__(GC::NT, GC::OCC* GC::NT / 256) bwd_stage_kerne
   }
   if (cols >= GC::BM)
     contract_tile<E, GC, false, false>(a, kind == 0, job, mt, n0, smem);
-  else if (2 * cols > GC::BM)
+  else if (!GC::SKIPS || 2 * cols > GC::BM)
     contract_tile<E, GC, true, false>(a, kind == 0, job, mt, n0, smem);
-  else
+  else if constexpr (GC::SKIPS)
     contract_tile<E, GC, true, true>(a, kind == 0, job, mt, n0, smem);
 }
 
@@ -1650,7 +1636,7 @@ template <> struct Cfg<Bf16> {
   // the last dH / dW column block when d leaves 1..64 columns past a multiple of
   // 256 (160 x 64 per wave, 0.7 fragment reads per MFMA)
   using MmWide = GemmDma<320, 256, 2, 4>;
-  using LogitsTail = GemmDma<256, 256, 2, 4, 64, 2, Bf16, true>;
+  using LogitsTail = GemmDma<256, 256, 2, 4, Bf16, true>;
   using Stream128 = Ring<256, 128, 4, 2, 3, Bf16>;  // forward on few tokens, see fwd_tile
   using Stream64 = Ring<128, 64, 4, 2, 6, Bf16>;
   // The backward's tile classes (StageArgs): 0: Logits, Tr256, Tr320; 1: Res128x64,
@@ -1659,24 +1645,24 @@ template <> struct Cfg<Bf16> {
   // d = 1000, V = 32003 98 / 74 / 76; float32 T = 256, d = 256, V = 2048 153 / 47 / 62 and
   // T = 2048, d = 2880, V = 50000 13961 / 13173 / 13273; class 3 against 0: bf16 T = 32768,
   // d = 2880, V = 201088 96.3 against 97.1 ms, T = 4096 12.60 against 12.38 ms.
-  using Tr256 = GemmDma<256, 256, 2, 4, 64, 2, Bf16, false, true>;
-  using Tr320 = GemmDma<320, 256, 2, 4, 64, 2, Bf16, false, true>;
-  using Res128 = GemmDma<128, 128, 2, 2, 64, 2, Bf16, true>;
-  using Tr128 = GemmDma<128, 128, 2, 2, 64, 2, Bf16, false, true>;
+  using Tr256 = GemmDma<256, 256, 2, 4, Bf16, false, true>;
+  using Tr320 = GemmDma<320, 256, 2, 4, Bf16, false, true>;
+  using Res128 = GemmDma<128, 128, 2, 2, Bf16, true>;
+  using Tr128 = GemmDma<128, 128, 2, 2, Bf16, false, true>;
   using Res128x64 = Ring<128, 64, 4, 2, 3, Bf16>;
   using Tr128x64 = Ring<128, 64, 4, 2, 3, Bf16, true>;
 };
 template <> struct Cfg<F32> {
   // The same direct-to-LDS ring and 256 x 256 tiles: 32 float32 k values per slice,
   // four 32x32x2 f32 MFMAs per fragment pair.
-  using Logits = GemmDma<256, 256, 2, 4, 64, 2, F32>;
-  using LogitsTail = GemmDma<256, 256, 2, 4, 64, 2, F32, true>;
+  using Logits = GemmDma<256, 256, 2, 4, F32>;
+  using LogitsTail = GemmDma<256, 256, 2, 4, F32, true>;
   using Stream128 = Ring<256, 128, 4, 2, 3, F32>;
   using Stream64 = Ring<128, 64, 4, 2, 6, F32>;
   using Mm = Logits;
-  using MmWide = GemmDma<320, 256, 2, 4, 64, 2, F32>;
-  using Res128 = GemmDma<128, 128, 2, 2, 64, 2, F32, true>;
-  using Tr128 = GemmDma<128, 128, 2, 2, 64, 2, F32, false, true>;
+  using MmWide = GemmDma<320, 256, 2, 4, F32>;
+  using Res128 = GemmDma<128, 128, 2, 2, F32, true>;
+  using Tr128 = GemmDma<128, 128, 2, 2, F32, false, true>;
   using Res128x64 = Ring<128, 64, 4, 2, 3, F32>;
   using Tr128x64 = Ring<128, 64, 4, 2, 3, F32, true>;
 };
