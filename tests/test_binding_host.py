@@ -130,7 +130,7 @@ def test_one_pass_takes_the_pointers():
 
 
 @pytest.mark.parametrize("case", sorted(set(FWD_CASES) - {"small workspace", "host tensors"}))
-def test_one_pass_refuses_forward(case):  # (the library judges the workspace's size)
+def test_one_pass_refuses_forward(case):  # (the library checks the workspace's size)
     assert _pass(_fwd_args(**FWD_CASES[case][0])) is None
 
 
